@@ -115,9 +115,8 @@ dtst_status dtst_basis_host(const dtst_desc* d, int dim, int kind, float* out, s
  *
  * The plan also fixes the kernel schedule of both chains (dtst_forward and
  * dtst_inverse_adj; dtst_inverse and dtst_forward_adj): where the shapes
- * allow it (K_t <= 8, at most 16 z modes per fold class, N_t^loc <= 32 and a
- * multiple of 4, K_y <= 32, K_z K_t <= 256) the t, z and y contractions run
- * as one launch; otherwise t + z and y are separate launches.  Same as
+ * allow it (K_t <= 8, at most 16 z modes per fold class, 4 <= N_t^loc <= 32,
+ * K_y <= 32, K_z K_t <= 256) the t, z and y contractions run as one launch; otherwise t + z and y are separate launches.  Same as
  * dtst_plan_ex(d, 0, out). */
 dtst_status dtst_plan(const dtst_desc* d, dtst_plan_t* out);
 
@@ -221,8 +220,8 @@ dtst_status dtst_block_epilogue(dtst_plan_t p, const float* x, const float* w_by
  * followed by the block epilogue,
  *   y = GELU( w_bypass x + inverse(yhat) ),
  * with the arrays, layouts, alignment and overlap rules of dtst_inverse and
- * dtst_block_epilogue.  Where the plan allows it (N_t^loc a multiple of 4 and
- * at most 32, C_in and C_out at most 32, at most 32 z modes per fold class,
+ * dtst_block_epilogue.  Where the plan allows it (N_t^loc even and at most 32,
+ * N_z^loc N_t^loc per z class a multiple of 4, C_in and C_out at most 32, at most 32 z modes per fold class,
  * the per-workgroup buffers within the LDS; see
  * dtst_plan_block_workspace_bytes) the z and t expansions and the epilogue
  * run as one kernel that writes y once and reads x once; otherwise, or with

@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "dtst_internal.h"
 
@@ -27,6 +28,9 @@ namespace {
 
 #include "gelu_as.h"
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));
+
 // ADDY: the accumulators start from y (block epilogue), else from the bias
 // (zero without one).  ACT: 1 applies GELU, 0 none.  OC: output channels per
 // pass over the input channels (the launcher picks C_out rounded up to a
@@ -35,9 +39,13 @@ template <int VEC, int ADDY, int ACT, int OC>
 __global__ void __launch_bounds__(256)
 pointwise_kernel(const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
                  float* __restrict__ y, int64_t V, int64_t total, int ci, int co) {
-  // VEC: 4 points per thread (V % 4 == 0, 16-byte accesses), else 1.
+  // VEC 1: 4 points per thread, V % 4 == 0, aligned 16-byte accesses; 2: the
+  // same for any V >= 4 (16-byte accesses at 4-byte alignment; the last
+  // thread of a batch entry takes its last four points and stores only those
+  // no other thread has); 0: one point per thread (V < 4).
   constexpr int P = VEC ? 4 : 1;
-  const int64_t VP = V / P;
+  const int64_t VP = (V + P - 1) / P;
+  using vec_t = std::conditional_t<VEC == 2, v4f_u, v4f>;
   // w (and the bias) in LDS: every lane reads the same entry (a broadcast),
   // which keeps them out of the scalar registers.
   extern __shared__ float sw[];
@@ -48,7 +56,8 @@ pointwise_kernel(const float* __restrict__ x, const float* __restrict__ w, const
   __syncthreads();
   for (int64_t idx = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; idx < total;
        idx += int64_t(gridDim.x) * blockDim.x) {
-    const int64_t b = idx / VP, n = (idx - b * VP) * P;
+    const int64_t b = idx / VP, n0 = (idx - b * VP) * P;
+    const int64_t n = VEC == 2 ? min(n0, V - P) : n0;
     const float* xb = x + b * ci * V + n;
     float* yb = y + b * co * V + n;
     for (int o0 = 0; o0 < co; o0 += OC) {
@@ -63,7 +72,7 @@ pointwise_kernel(const float* __restrict__ x, const float* __restrict__ w, const
 #pragma unroll
           for (int p = 0; p < P; ++p) acc[oo][p] = sb[o];
         } else if constexpr (VEC) {
-          const float4 v = *reinterpret_cast<const float4*>(yp);
+          const vec_t v = *reinterpret_cast<const vec_t*>(yp);
           acc[oo][0] = v.x;
           acc[oo][1] = v.y;
           acc[oo][2] = v.z;
@@ -76,7 +85,7 @@ pointwise_kernel(const float* __restrict__ x, const float* __restrict__ w, const
       for (int i = 0; i < ci; ++i) {
         float xv[P];
         if constexpr (VEC) {
-          const float4 v = *reinterpret_cast<const float4*>(xb + int64_t(i) * V);
+          const vec_t v = *reinterpret_cast<const vec_t*>(xb + int64_t(i) * V);
           xv[0] = v.x;
           xv[1] = v.y;
           xv[2] = v.z;
@@ -100,7 +109,13 @@ pointwise_kernel(const float* __restrict__ x, const float* __restrict__ w, const
 #pragma unroll
         for (int p = 0; p < P; ++p) r[p] = ACT ? gelu_as(acc[oo][p]) : acc[oo][p];
         if constexpr (VEC) {
-          *reinterpret_cast<float4*>(yp) = make_float4(r[0], r[1], r[2], r[3]);
+          if (VEC == 1 || n == n0) {
+            *reinterpret_cast<vec_t*>(yp) = vec_t{r[0], r[1], r[2], r[3]};
+          } else {
+#pragma unroll
+            for (int p = 1; p < P; ++p)
+              if (n + p >= n0) yp[p] = r[p];
+          }
         } else {
           *yp = r[0];
         }
@@ -113,24 +128,24 @@ pointwise_kernel(const float* __restrict__ x, const float* __restrict__ w, const
 template <int ADDY, int ACT, int OC>
 int launch_pw_oc(const float* x, const float* w, const float* bias, float* y, int64_t B, int64_t ci, int64_t co,
                  int64_t V, void* stream) {
-  const bool vec = V % 4 == 0;
-  const int64_t total = B * (vec ? V / 4 : V);
+  // V % 4 != 0 (channels not 16-byte aligned) took one point per thread
+  // before: 367 us against 336 us for 6 -> 11 channels of 17 x 243 x 131 x 27.
+  const int vec = V % 4 == 0 ? 1 : (V >= 4 ? 2 : 0);
+  const int64_t total = B * (vec ? (V + 3) / 4 : V);
   const int64_t cap = int64_t(1) << 20;
   const int64_t blocks = std::min<int64_t>((total + 255) / 256, cap);
   hipStream_t s = static_cast<hipStream_t>(stream);
   const size_t lds = (size_t(ci) * co + (ADDY ? 0 : co)) * sizeof(float);
-  const void* fn = vec ? reinterpret_cast<const void*>(pointwise_kernel<1, ADDY, ACT, OC>)
-                       : reinterpret_cast<const void*>(pointwise_kernel<0, ADDY, ACT, OC>);
+  auto* fn = vec == 1   ? pointwise_kernel<1, ADDY, ACT, OC>
+             : vec == 2 ? pointwise_kernel<2, ADDY, ACT, OC>
+                        : pointwise_kernel<0, ADDY, ACT, OC>;
   if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
   }
-  if (vec)
-    hipLaunchKernelGGL((pointwise_kernel<1, ADDY, ACT, OC>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, s,
-                       x, w, bias, y, V, total, static_cast<int>(ci), static_cast<int>(co));
-  else
-    hipLaunchKernelGGL((pointwise_kernel<0, ADDY, ACT, OC>), dim3(static_cast<unsigned>(blocks)), dim3(256), lds, s,
-                       x, w, bias, y, V, total, static_cast<int>(ci), static_cast<int>(co));
+  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, s, x, w, bias, y, V, total,
+                     static_cast<int>(ci), static_cast<int>(co));
   return hipGetLastError();
 }
 

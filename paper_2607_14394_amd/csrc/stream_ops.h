@@ -17,6 +17,34 @@ __device__ __forceinline__ void store_stream(float* p, float a, float b, float c
   __builtin_nontemporal_store(v4f{a, b, c, d}, reinterpret_cast<v4f*>(p));
 }
 
+// 16-byte accesses at any 4-byte boundary (rows of N_t floats with N_t % 4
+// != 0); the hardware takes them as one instruction.
+typedef float v4f_u __attribute__((ext_vector_type(4), aligned(4)));
+
+// t positions of a lane's 16-byte chunks: chunk h of lane group g covers
+// t_first .. t_first + 3 of the extent (t folded: chunk h < TH/2 of the first
+// half, chunk h + TH/2 the same positions of the second half).  A chunk that
+// would run past the end of the extent is read and written at t_start, its
+// last four positions; a chunk that starts past it does not exist.  N_t >= 4
+// (t folded: N_t >= 8).
+template <int TH, int TF>
+__device__ __forceinline__ int t_first(int h, int g, int nt) {
+  if (TF) return 16 * (h % (TH / 2 > 0 ? TH / 2 : 1)) + 4 * g + (h >= TH / 2 ? nt / 2 : 0);
+  return 16 * h + 4 * g;
+}
+template <int TH, int TF>
+__device__ __forceinline__ int t_end(int h, int nt) {
+  return TF && h < TH / 2 ? nt / 2 : nt;
+}
+template <int TH, int TF>
+__device__ __forceinline__ int t_start(int h, int g, int nt) {
+  return min(t_first<TH, TF>(h, g, nt), t_end<TH, TF>(h, nt) - 4);
+}
+template <int TH, int TF>
+__device__ __forceinline__ bool t_chunk(int h, int g, int nt) {
+  return t_first<TH, TF>(h, g, nt) < t_end<TH, TF>(h, nt);
+}
+
 struct StreamArgs {
   int64_t rows;
   int nt, nz, kt, kz, zh, zt, vec;

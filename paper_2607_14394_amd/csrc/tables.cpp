@@ -175,10 +175,12 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   sc.mt = kcp / 8;
   sc.zh = sc.nz / sc.ncls;
   sc.zt = static_cast<int>(ceil_div(sc.zh, 16));
-  sc.vec = (sc.nt % 4 == 0) ? 1 : 0;
+  sc.vec = sc.nt >= 4 ? 1 : 0;
   // t folds (even k_t from x(t) + x(t + N_t/2), odd k_t from the difference)
-  // in the split kernels when the shard holds the whole t extent of 32.
-  sc.tf = (sc.ct == 2 && sc.th == 2 && sc.nt == 32 && d->n_local[3] == d->n_global[3]) ? 1 : 0;
+  // in the split kernels when the shard holds the whole even t extent and
+  // each half is one 16-wide group (17 <= N_t <= 32; the kernels read the two
+  // halves at any 4-byte alignment).
+  sc.tf = (sc.ct == 2 && sc.th == 2 && sc.nt % 2 == 0 && d->n_local[3] == d->n_global[3]) ? 1 : 0;
   sc.lds_bytes = size_t(sc.ncls) * sc.zt * z_blocks(sc) * 64 * 16;
   if (sc.lds_bytes > 160 * 1024) {
     *err = "z basis image exceeds the 160 KiB LDS of a workgroup";
@@ -357,8 +359,15 @@ inline void bval(const dtst_desc& d, int dim, int64_t p, int64_t j, double* re, 
   twiddle(d.n_global[dim], retained_index(d, dim, p), d.offset[dim] + j, re, im);
 }
 
+// First t of the 16-byte chunk that starts at t0 of an extent of `lim`
+// values: a chunk that would run past the end starts at the last four values
+// (t_start of the kernels; extents below 4 have no such chunks).
+int t_chunk_start(int t0, int lim) { return lim >= 4 ? std::min(t0, lim - 4) : t0; }
+
 // t image of the forward streaming kernel (B operand of the first MFMA):
-// entry ((h*4 + j)*CT + ct)*64 + lane holds Bt'[t][c] with t = 16h + 4g + j,
+// entry ((h*4 + j)*CT + ct)*64 + lane holds Bt'[t][c] with t = 16h + 4g + j
+// (the chunk's start plus j where the chunk starts early; zero for the values
+// an earlier chunk also holds),
 // c = 16ct + m (m = lane & 15, g = lane >> 4); c < 8CT is Re B_t[kt=c][t],
 // otherwise Im B_t[kt = c - 8CT][t]; times scale(kt).  t-folded (tf), only
 // t < N_t/2 is filled and column m of tile ct is k_t = 2(m & 7) + ct, Re for
@@ -374,12 +383,12 @@ void t_forward_image(const Derived& dv, bool adjoint_of_inverse, float* dst) {
       for (int ct = 0; ct < sc.ct; ++ct)
         for (int lane = 0; lane < 64; ++lane) {
           const int m = lane & 15, g = lane >> 4;
-          const int t = 16 * h + 4 * g + j;
+          const int t0 = 16 * h + 4 * g, t = t_chunk_start(t0, tlim) + j;
           const int c = 16 * ct + m;
           const bool is_re = sc.tf ? m < 8 : c < ktp;
           const int kt = sc.tf ? 2 * (m & 7) + ct : (is_re ? c : c - ktp);
           double v = 0.0;
-          if (t < tlim && kt < sc.kt) {
+          if (t >= t0 && t < tlim && kt < sc.kt) {
             double re, im;
             bval(d, 3, kt, t, &re, &im);
             double s = adjoint_of_inverse ? half_weight(d.n_global[3], kt) / ntot : 1.0;
@@ -435,7 +444,9 @@ void z_forward_image(const Derived& dv, float* dst) {
 }
 
 // t image of the inverse streaming kernel (A operand of its second MFMA):
-// entry ((mt*CT + ct)*4 + i)*64 + lane holds A[t][c] with t = 16mt + m,
+// entry ((mt*CT + ct)*4 + i)*64 + lane holds A[t][c] with t = 16mt + m (rows
+// 4q..4q+3 of a chunk that starts early, or past the end, are the last four t
+// again: every store of such a chunk writes values of the row),
 // c = 16ct + 4g + i: Re C_t[t][kt] for c < 8CT, -Im C_t[t][kt] otherwise,
 // where C_t[t][kt] = scale(kt) conj(B_t[kt][t]).  t-folded (tf), only
 // t < N_t/2 is filled and K index 4g + i of tile ct is
@@ -455,7 +466,7 @@ void t_inverse_image(const Derived& dv, bool is_inverse, float* dst) {
       for (int i = 0; i < 4; ++i)
         for (int lane = 0; lane < 64; ++lane) {
           const int m = lane & 15, g = lane >> 4;
-          const int t = 16 * mt + m;
+          const int t = t_chunk_start(16 * mt + (m & ~3), tlim) + (m & 3);
           const int c = 16 * ct + 4 * g + i;
           // t-folded: tile ct holds part ct (0 Re, 1 -Im) of k_t = 2(2g + (i & 1)) + (i >> 1)
           const bool is_re = sc.tf ? ct == 0 : (sc.mt == 1 ? i < 2 : c < ktp);

@@ -1,0 +1,98 @@
+"""Parity at t extents that are not whole 16-byte chunks: a row's last t chunk
+then starts early (its values overlap the previous chunk's), rows lie at any
+4-byte alignment, and the t fold of k_t > 8 splits an even extent at any
+position.  Extents at the edges of the t groups (16, 32), every remainder mod
+4, folded and unfolded z, ragged z tiles, both schedules; the fused inverse +
+block epilogue at even extents; the point-wise layer at point counts that are
+not multiples of 4."""
+
+import numpy as np
+import pytest
+
+import oracle as O
+from gpu_common import Guarded, check, desc_of, dev, geometry, np_of, rand_cplx, rand_real, say, torch_gpu
+
+pytestmark = pytest.mark.gpu
+
+# (N_t, k_t): below one chunk, one chunk, each remainder, around the 16- and 32-wide groups
+EXTENTS = [(3, 2), (4, 3), (5, 3), (6, 2), (7, 4), (13, 7), (15, 8), (17, 5), (17, 9), (18, 10), (19, 10), (21, 11),
+           (22, 12), (26, 9), (30, 16), (31, 8), (31, 16), (33, 6), (34, 16), (47, 3), (63, 13)]
+# (N_x, N_y, N_z), k_max of z: folded whole tiles, folded ragged tile, odd N_z
+GRIDS = [((3, 4, 32), 5), ((2, 6, 26), 3), ((3, 5, 19), 7)]
+
+
+@pytest.mark.parametrize("split", [False, True], ids=["default", "split"])
+@pytest.mark.parametrize("nt,kt", EXTENTS)
+def test_transforms(nt, kt, split):
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    for (nx, ny, nz), kz in GRIDS:
+        n = (nx, ny, nz, nt)
+        g = geometry(n, n, (0, 0, 0, 0), (1, 2, kz), kt, 2, 3, 2)
+        say(f"[t chunks] n={n} kt={kt} kz={kz} split={split}")
+        plan = D.Plan(desc_of(g), flags=D.PLAN_SPLIT_SCHEDULE if split else 0)
+        x, gy = rand_real((2, 3) + n, 41), rand_real((2, 2) + n, 42)
+        yh, gxh = rand_cplx((2, 2) + g.K, 43), rand_cplx((2, 3) + g.K, 44)
+        xhat = Guarded(torch, plan.spectral_shape(3), torch.complex64)
+        gyh = Guarded(torch, plan.spectral_shape(2), torch.complex64)
+        y = Guarded(torch, plan.spatial_shape(2), torch.float32)
+        gx = Guarded(torch, plan.spatial_shape(3), torch.float32)
+        plan.forward(dev(torch, x), xhat.t)
+        plan.inverse_adj(dev(torch, gy), gyh.t)
+        plan.inverse(dev(torch, yh), y.t)
+        plan.forward_adj(dev(torch, gxh), gx.t)
+        torch.cuda.synchronize()
+        check(np_of(xhat.t), O.forward(x, g), "forward")
+        check(np_of(gyh.t), O.inverse_adj(gy, g), "inverse_adj")
+        check(np_of(y.t), O.inverse(yh, g), "inverse")
+        check(np_of(gx.t), O.forward_adj(gxh, g), "forward_adj")
+        for b in (xhat, gyh, y, gx):
+            assert b.guards_intact()
+        plan.close()
+
+
+@pytest.mark.parametrize("c", [3, 16, 20, 32])
+@pytest.mark.parametrize("nt,kt", [(6, 3), (18, 10), (22, 5), (26, 12), (28, 9), (30, 7), (30, 16)])
+def test_inverse_block(nt, kt, c):
+    """Even extents: the fused kernel (whole and ragged last z tiles) with each channel class."""
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    for nz, kz in ((32, 5), (26, 3) if nt % 4 == 0 else (20, 3)):
+        n = (2, 3, nz, nt)
+        g = geometry(n, n, (0, 0, 0, 0), (1, 1, kz), kt, 2, c, c)
+        say(f"[t chunks, block] n={n} kt={kt} c={c}")
+        plan = D.Plan(desc_of(g))
+        assert plan.block_fused == 1
+        yh, x = rand_cplx((2, c) + g.K, 51), rand_real((2, c) + n, 52)
+        wb = (rand_real((c, c), 53) / np.sqrt(c)).astype(np.float32)
+        y = Guarded(torch, plan.spatial_shape(c), torch.float32)
+        plan.inverse_block(dev(torch, yh), dev(torch, x), dev(torch, wb), y.t)
+        torch.cuda.synchronize()
+        check(np_of(y.t), O.block_epilogue(x, wb, O.inverse(yh, g)), "inverse + block epilogue")
+        assert y.guards_intact()
+        plan.close()
+
+
+@pytest.mark.parametrize("points", [1, 3, 4, 5, 6, 7, 1022])
+def test_pointwise_and_epilogue(points):
+    """Point counts around the 4-point accesses; in place (epilogue) and out of place (point-wise layer)."""
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    ci, co, batch = 5, 18, 3
+    x, w, b = rand_real((batch, ci, points), 61), rand_real((co, ci), 62), rand_real((co,), 63)
+    y = Guarded(torch, (batch, co, points), torch.float32)
+    D.dtst_pointwise(dev(torch, x), dev(torch, w), dev(torch, b), y.t, act=1)
+    torch.cuda.synchronize()
+    check(np_of(y.t), O.pointwise(x, w, b, act=True), "pointwise")
+    assert y.guards_intact()
+    n = (1, 1, 1, points) if points < 64 else (1, 1, 73, 14)
+    g = geometry((2, 2, max(n[2], 2), n[3]), n, (0, 0, 0, 0), (1, 1, 1), 1, batch, ci, co)
+    plan = D.Plan(desc_of(g))
+    x, y0 = rand_real((batch, ci) + n, 64), rand_real((batch, co) + n, 65)
+    y = Guarded(torch, (batch, co) + n, torch.float32)
+    y.t.copy_(dev(torch, y0))
+    plan.block_epilogue(dev(torch, x), dev(torch, w), y.t)
+    torch.cuda.synchronize()
+    check(np_of(y.t), O.block_epilogue(x, w, y0), "block epilogue")
+    assert y.guards_intact()
+    plan.close()
