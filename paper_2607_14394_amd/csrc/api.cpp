@@ -159,24 +159,38 @@ int timed(int role, void* stream, F&& launch) {
 // Forward-direction chain: streaming t+z, then y (one fused launch when the
 // plan allows it), then x (with accumulate).
 dtst_status run_forward_chain(const dtst_plan_st* p, int64_t channels, const float* x, void* xhat,
-                              int accumulate, void* ws, const float* timg, void* stream) {
+                              int accumulate, void* ws, bool adjoint_of_inverse, void* stream) {
   const dtst::Derived& dv = p->dv;
+  const dtst::Images& im = dv.img;
+  const float* timg = p->blob + (adjoint_of_inverse ? im.t_fwd_adjoint_of_inverse : im.t_fwd);
   const int64_t B = dv.d.batch;
   if (B == 0) return ok();
   char* w1 = static_cast<char*>(ws);
   char* w2 = w1 + dv.w1_bytes;
   const int64_t planes = B * channels * dv.d.n_local[0];
   const int64_t rows = planes * dv.d.n_local[1];
+  const float* zr_timg = p->blob + (adjoint_of_inverse ? im.zr_t_fwd_adjoint_of_inverse : im.zr_t_fwd);
   int e;
-  if (dv.sc.fuse_y) {
+  if (dv.zr.fwd == 2) {
+    w2 = w1;  // the planes' parts, no W1
+    e = timed(K_FWD_TZY, stream, [&] {
+      return dtst::launch_fwd_zty(dv.zr, dv.sc, dv.ay_f, x, w2, planes, static_cast<int>(dv.d.n_local[1]), zr_timg,
+                                  p->blob + im.zr_z_fwd, p->blob + im.zr_phase, p->blob + im.y_fwd, stream);
+    });
+    if (e != hipSuccess) return device_status(e, "z+t+y contraction launch");
+  } else if (dv.sc.fuse_y && !dv.zr.fwd) {
     e = timed(K_FWD_TZY, stream, [&] {
       return dtst::launch_fwd_tzy(dv.sc, dv.ay_f, x, w2, planes, static_cast<int>(dv.d.n_local[1]), timg,
                                   p->blob + dv.img.z_fwd, p->blob + dv.img.y_fwd, stream);
     });
     if (e != hipSuccess) return device_status(e, "t+z+y contraction launch");
   } else {
-    e = timed(K_FWD_TZ, stream,
-              [&] { return dtst::launch_fwd_tz(dv.sc, x, w1, rows, timg, p->blob + dv.img.z_fwd, stream); });
+    e = timed(K_FWD_TZ, stream, [&] {
+      if (dv.zr.fwd)
+        return dtst::launch_fwd_zrow(dv.zr, dv.sc, x, w1, rows, zr_timg, p->blob + im.zr_z_fwd,
+                                     p->blob + im.zr_phase, stream);
+      return dtst::launch_fwd_tz(dv.sc, x, w1, rows, timg, p->blob + im.z_fwd, stream);
+    });
     if (e != hipSuccess) return device_status(e, "t+z contraction launch");
     e = timed(K_AXIS_FWD_Y, stream, [&] {
       return dtst::launch_axis(dv.ay_f, planes, w1, w2, p->blob + dv.img.y_fwd, 0, stream);
@@ -193,8 +207,10 @@ dtst_status run_forward_chain(const dtst_plan_st* p, int64_t channels, const flo
 // Inverse-direction chain: x, then y, then streaming z+t with Re (y, z and t
 // in one launch when the plan allows it).
 dtst_status run_inverse_chain(const dtst_plan_st* p, int64_t channels, const void* yhat, float* y, void* ws,
-                              const float* timg, void* stream) {
+                              bool adjoint_of_forward, void* stream) {
   const dtst::Derived& dv = p->dv;
+  const dtst::Images& im = dv.img;
+  const float* timg = p->blob + (adjoint_of_forward ? im.t_inv_adjoint_of_forward : im.t_inv);
   const int64_t B = dv.d.batch;
   if (B == 0) return ok();
   char* v2 = static_cast<char*>(ws);    // (.., Nx, Ny, Kz, Kt)
@@ -204,7 +220,15 @@ dtst_status run_inverse_chain(const dtst_plan_st* p, int64_t channels, const voi
   });
   if (e != hipSuccess) return device_status(e, "x expansion launch");
   const int64_t planes = B * channels * dv.d.n_local[0];
-  if (dv.sc.fuse_y) {
+  const float* zr_timg = p->blob + (adjoint_of_forward ? im.zr_t_inv_adjoint_of_forward : im.zr_t_inv);
+  if (dv.zr.inv == 2) {
+    e = timed(K_INV_YZT, stream, [&] {
+      return dtst::launch_inv_yzrow(dv.zr, dv.sc, dv.ay_i, v1, y, planes, static_cast<int>(dv.d.n_local[1]), zr_timg,
+                                    p->blob + im.zr_z_inv, p->blob + im.zr_phase_inv, p->blob + im.y_inv, stream);
+    });
+    return e == hipSuccess ? ok() : device_status(e, "y+t+z expansion launch");
+  }
+  if (dv.sc.fuse_y && !dv.zr.inv) {
     e = timed(K_INV_YZT, stream, [&] {
       return dtst::launch_inv_yzt(dv.sc, dv.ay_i, v1, y, planes, static_cast<int>(dv.d.n_local[1]), timg,
                                   p->blob + dv.img.z_inv, p->blob + dv.img.y_inv, stream);
@@ -217,8 +241,12 @@ dtst_status run_inverse_chain(const dtst_plan_st* p, int64_t channels, const voi
   });
   if (e != hipSuccess) return device_status(e, "y expansion launch");
   const int64_t rows = planes * dv.d.n_local[1];
-  e = timed(K_INV_ZT, stream,
-            [&] { return dtst::launch_inv_zt(dv.sc, v2, y, rows, timg, p->blob + dv.img.z_inv, stream); });
+  e = timed(K_INV_ZT, stream, [&] {
+    if (dv.zr.inv)
+      return dtst::launch_inv_zrow(dv.zr, dv.sc, v2, y, rows, zr_timg, p->blob + im.zr_z_inv,
+                                   p->blob + im.zr_phase_inv, stream);
+    return dtst::launch_inv_zt(dv.sc, v2, y, rows, timg, p->blob + im.z_inv, stream);
+  });
   if (e != hipSuccess) return device_status(e, "z+t expansion launch");
   return ok();
 }
@@ -316,6 +344,9 @@ dtst_status dtst_plan_ex(const dtst_desc* d, uint32_t flags, dtst_plan_t* out) {
     return fail(DTST_ERR_DEVICE, std::string("hipMemcpy of the basis tables: ") + hipGetErrorString(e));
   }
   int pe = dtst::prepare_stream(&p->dv.sc);
+  if (pe == hipSuccess) pe = dtst::prepare_zrow(&p->dv.zr, p->dv.sc.nt);
+  if (pe == hipSuccess && p->dv.zr.fwd == 2) pe = dtst::prepare_fwd_zty(&p->dv.zr);
+  if (pe == hipSuccess && p->dv.zr.inv == 2) pe = dtst::prepare_inv_yzrow(p->dv.zr, p->dv.sc.nt);
   if (pe == hipSuccess && p->dv.blk &&
       dtst::prepare_block_zt(p->dv.sb, p->dv.d.c_in, p->dv.d.c_out, &p->dv.grid_blk) != hipSuccess) {
     // the device does not take the fused block kernel at this size: the
@@ -374,7 +405,7 @@ dtst_status dtst_forward(dtst_plan_t p, const float* x, void* xhat, int accumula
   if (accumulate != 0 && accumulate != 1) return fail(DTST_ERR_INVALID_ARG, "accumulate must be 0 or 1");
   DeviceGuard guard(p->device);
   if (guard.err != hipSuccess) return device_status(guard.err, "hipSetDevice");
-  return run_forward_chain(p, p->dv.d.c_in, x, xhat, accumulate, workspace, p->blob + p->dv.img.t_fwd, stream);
+  return run_forward_chain(p, p->dv.d.c_in, x, xhat, accumulate, workspace, false, stream);
 }
 
 dtst_status dtst_forward_noalloc(dtst_plan_t p, const float* x, void* xhat, int accumulate, void* stream) {
@@ -392,7 +423,7 @@ dtst_status dtst_forward_noalloc(dtst_plan_t p, const float* x, void* xhat, int 
   void* scratch = nullptr;  // found at plan creation on this device
   const int se = dtst::scratch_address(p->device, &scratch);
   if (se != hipSuccess) return device_status(se, "scratch array lookup");
-  return run_forward_chain(p, p->dv.d.c_in, x, xhat, accumulate, scratch, p->blob + p->dv.img.t_fwd, stream);
+  return run_forward_chain(p, p->dv.d.c_in, x, xhat, accumulate, scratch, false, stream);
 }
 
 dtst_status dtst_inverse_adj(dtst_plan_t p, const float* g_y, void* g_yhat, int accumulate, void* workspace,
@@ -405,8 +436,7 @@ dtst_status dtst_inverse_adj(dtst_plan_t p, const float* g_y, void* g_yhat, int 
   if (accumulate != 0 && accumulate != 1) return fail(DTST_ERR_INVALID_ARG, "accumulate must be 0 or 1");
   DeviceGuard guard(p->device);
   if (guard.err != hipSuccess) return device_status(guard.err, "hipSetDevice");
-  return run_forward_chain(p, p->dv.d.c_out, g_y, g_yhat, accumulate, workspace,
-                           p->blob + p->dv.img.t_fwd_adjoint_of_inverse, stream);
+  return run_forward_chain(p, p->dv.d.c_out, g_y, g_yhat, accumulate, workspace, true, stream);
 }
 
 dtst_status dtst_inverse(dtst_plan_t p, const void* yhat, float* y, void* workspace, size_t workspace_bytes,
@@ -418,7 +448,7 @@ dtst_status dtst_inverse(dtst_plan_t p, const void* yhat, float* y, void* worksp
   DTST_TRY(check_ws(p, workspace, workspace_bytes));
   DeviceGuard guard(p->device);
   if (guard.err != hipSuccess) return device_status(guard.err, "hipSetDevice");
-  return run_inverse_chain(p, p->dv.d.c_out, yhat, y, workspace, p->blob + p->dv.img.t_inv, stream);
+  return run_inverse_chain(p, p->dv.d.c_out, yhat, y, workspace, false, stream);
 }
 
 dtst_status dtst_forward_adj(dtst_plan_t p, const void* g_xhat, float* g_x, void* workspace,
@@ -430,8 +460,7 @@ dtst_status dtst_forward_adj(dtst_plan_t p, const void* g_xhat, float* g_x, void
   DTST_TRY(check_ws(p, workspace, workspace_bytes));
   DeviceGuard guard(p->device);
   if (guard.err != hipSuccess) return device_status(guard.err, "hipSetDevice");
-  return run_inverse_chain(p, p->dv.d.c_in, g_xhat, g_x, workspace,
-                           p->blob + p->dv.img.t_inv_adjoint_of_forward, stream);
+  return run_inverse_chain(p, p->dv.d.c_in, g_xhat, g_x, workspace, true, stream);
 }
 
 dtst_status dtst_mix(dtst_plan_t p, const void* xhat, const void* w_shard, void* yhat, int64_t m0, int64_t m1,
@@ -560,7 +589,7 @@ dtst_status dtst_inverse_block(dtst_plan_t p, const void* yhat, const float* x, 
   DeviceGuard guard(p->device);
   if (guard.err != hipSuccess) return device_status(guard.err, "hipSetDevice");
   if (!dv.blk) {
-    DTST_TRY(run_inverse_chain(p, dv.d.c_out, yhat, y, workspace, p->blob + dv.img.t_inv, stream));
+    DTST_TRY(run_inverse_chain(p, dv.d.c_out, yhat, y, workspace, false, stream));
     return run_block_epilogue(p, x, w_bypass, y, stream);
   }
   // x expansion into W2, y expansion into W1, then z + t with the epilogue

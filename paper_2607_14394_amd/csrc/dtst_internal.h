@@ -55,6 +55,31 @@ struct StreamCfg {
   int grid_fused = 0;  // resident workgroups of fwd_tzy_kernel
 };
 
+// Row kernels that contract z before t and expand t before z (k_zrow.hip).
+//   fwd    0: not used; 1: in place of the t + z launch of the split schedule;
+//          2: with the y contraction in the same launch (k_zrow_y.hip)
+//   inv    0: not used; 1: in place of the z + t launch of the split schedule;
+//          2: with the y expansion in the same launch (k_zrow_yi.hip)
+//   th     t groups of 16
+//   fold   1 when the shard holds all of z: rows z and N_z - 1 - z together
+//   ntl    16-mode tiles of k = 0 .. k_max (forward)
+//   ns     K steps of four modes covering k = 0 .. k_max (inverse): 2, 3, 4, 6, 8
+//   mk     1 when K_t <= 8 (Br and Bi rows of one k_t tile), else 2
+//   np     z positions (ceil(N_z / 2) folded), np2 of them with a partner row
+//   parts  fwd 2: runs of slot groups a plane is divided into, each with its
+//          own partial y sums in W2 (N_x planes of `parts` entries)
+//   ncy, kyt, fused_mrow: as in StreamCfg
+struct ZRowCfg {
+  int fwd = 0, inv = 0;
+  int th = 1, fold = 0, ntl = 1, ns = 2, mk = 1;
+  int np = 0, np2 = 0;
+  int steps = 0, units = 0;  // ceil(np / 4), ceil(np / 16)
+  int fmode = 1;             // forward: 2 when every position of every unit has its rows (no masks)
+  int parts = 1, ncy = 1, kyt = 1, fused_mrow = 0;
+  size_t fused_lds_bytes = 0, ifused_lds_bytes = 0;  // fwd 2; inv 2
+  int grid_fwd = 0, grid_inv = 0, grid_fused = 0;  // resident workgroups (prepare_zrow, prepare_fwd_zty)
+};
+
 // Generic complex contraction along a middle axis:
 //   out[b][k][n] (+)= sum_j basis[k][j] in[b][j][n],
 // b < nb, j < J, k < KO, n < NN (complex elements).
@@ -76,6 +101,7 @@ struct AxisCfg {
   // factors of their three-product form), 2 (Re, Im) for the y images of the
   // fused stream kernels
   int parts = 3;
+  int jdup = 1;  // consecutive j that share the basis value of j / jdup (forward)
 };
 
 // Float offsets of each kernel-ready image inside the plan's device blob.
@@ -86,6 +112,10 @@ struct Images {
   size_t z_inv = 0;                                // streaming inverse, LDS image
   size_t y_fwd = 0, x_fwd = 0, y_inv = 0, x_inv = 0;  // axis images
   size_t z_blk = 0, t_blk = 0;                         // fused inverse + block epilogue
+  // z-first rows: forward z basis, mode phases and t bases; inverse z basis,
+  // mode phases and t bases (only where ZRowCfg::fwd or inv)
+  size_t zr_z_fwd = 0, zr_phase = 0, zr_t_fwd = 0, zr_t_fwd_adjoint_of_inverse = 0;
+  size_t zr_z_inv = 0, zr_phase_inv = 0, zr_t_inv = 0, zr_t_inv_adjoint_of_forward = 0;
   size_t y_blk = 0;  // y expansion of dtst_inverse_block (y_inv unless the plan fuses y)
   size_t total = 0;
 };
@@ -95,6 +125,7 @@ struct Derived {
   int64_t K[4] = {0, 0, 0, 0};
   int64_t M = 0;
   StreamCfg sc;
+  ZRowCfg zr;
   AxisCfg ay_f, ax_f, ax_i, ay_i;  // per-channel shapes; nb is per (b, c) below
   AxisCfg ay_b;                    // the inverse y of dtst_inverse_block's separate y launch
   size_t ws_bytes = 0;
@@ -140,6 +171,23 @@ int launch_inv_yzt(const StreamCfg& c, const AxisCfg& ay, const void* in, float*
                    const float* timg, const float* zimg, const float* yimg, void* stream);
 int launch_inv_zt(const StreamCfg& c, const void* in, float* y, int64_t rows,
                   const float* timg, const float* zimg, void* stream);
+// The z-first row kernels (k_zrow.hip): forward rows into (rows x K_z K_t)
+// complex, inverse rows out of them.
+int prepare_zrow(ZRowCfg* c, int nt);
+int prepare_fwd_zty(ZRowCfg* c);
+// Forward z + t + y: `planes` planes of ny rows into (planes x parts x K_y x
+// K_z K_t) complex partial sums; ay is the forward y contraction (image yimg).
+int launch_fwd_zty(const ZRowCfg& c, const StreamCfg& s, const AxisCfg& ay, const float* x, void* out, int64_t planes,
+                   int ny, const float* timg, const float* zimg, const float* phase, const float* yimg, void* stream);
+int launch_fwd_zrow(const ZRowCfg& c, const StreamCfg& s, const float* x, void* out, int64_t rows, const float* timg,
+                    const float* zimg, const float* phase, void* stream);
+int launch_inv_zrow(const ZRowCfg& c, const StreamCfg& s, const void* in, float* y, int64_t rows, const float* timg,
+                    const float* zimg, const float* phase, void* stream);
+// Inverse y + t + z of `planes` planes; ay is the inverse y expansion.
+int prepare_inv_yzrow(const ZRowCfg& c, int nt);
+int launch_inv_yzrow(const ZRowCfg& c, const StreamCfg& s, const AxisCfg& ay, const void* in, float* y, int64_t planes,
+                     int ny, const float* timg, const float* zimg, const float* phase, const float* yimg,
+                     void* stream);
 // Fused inverse z + t expansion and block epilogue (k_block_zt.hip):
 //   y[b,o,.] = GELU(w x[b,.,.] + zt-expansion of in[b,o,.]) over the
 // batch * nxy (b, x, y) rows; in is the y-expanded spectrum

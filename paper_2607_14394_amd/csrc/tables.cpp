@@ -22,12 +22,41 @@ constexpr double kTwoPi = 6.283185307179586476925286766559;
 inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline size_t round_up(size_t a, size_t b) { return (a + b - 1) / b * b; }
 
+// exp(-2 pi i r / N) of every r < N for the few N of one plan: the images take
+// each value many times over (every lane of every tile).  Filled on demand
+// while build_images runs, on its thread; larger N are evaluated directly.
+struct TwiddleTables {
+  struct Table {
+    int64_t N;
+    std::vector<double> v;  // (re, im), NaN until evaluated
+  };
+  std::vector<Table> tables;
+  double* entry(int64_t N, int64_t r) {
+    if (N > 4096) return nullptr;
+    for (Table& t : tables)
+      if (t.N == N) return &t.v[2 * r];
+    tables.push_back({N, std::vector<double>(2 * N, std::numeric_limits<double>::quiet_NaN())});
+    return &tables.back().v[2 * r];
+  }
+};
+thread_local TwiddleTables* g_twiddles = nullptr;
+
 // exp(-2 pi i r / N) with r = (k * n) mod N, k, n >= 0.
 inline void twiddle(int64_t N, int64_t k, int64_t n, double* re, double* im) {
   const int64_t r = ((k % N) * (n % N)) % N;
+  double* e = g_twiddles ? g_twiddles->entry(N, r) : nullptr;
+  if (e && e[0] == e[0]) {
+    *re = e[0];
+    *im = e[1];
+    return;
+  }
   const double ang = kTwoPi * static_cast<double>(r) / static_cast<double>(N);
   *re = std::cos(ang);
   *im = -std::sin(ang);
+  if (e) {
+    e[0] = *re;
+    e[1] = *im;
+  }
 }
 
 // Real-inverse weight of stored t index kt (Sec. V-A inverse, half spectrum).
@@ -45,6 +74,39 @@ inline int axis_image_classes(const AxisCfg& a) { return a.fold == 2 ? 2 : (a.fo
 // z tile): mt, plus mt / 2 when t folds (the three-product form's third
 // operand, see z_forward_image and z_inverse_image).
 inline int z_blocks(const StreamCfg& s) { return s.tf ? 3 * s.mt / 2 : s.mt; }
+
+// Matrix instructions per row of the t-first kernels (either direction) and
+// of the z-first ones.
+int t_first_cost(const StreamCfg& s) {
+  const int t = s.ncls * s.th * 4 * s.ct / (s.tf ? 2 : 1);
+  const int z = s.ncls * (s.tf ? 3 * s.mt / 2 : s.mt * s.ct) * 4;
+  return s.zt * (t + z);
+}
+int z_first_fwd_cost(const ZRowCfg& z) { return z.ntl * 2 * z.th * (z.steps + 4 * z.mk); }
+int z_first_inv_cost(const ZRowCfg& z) { return 2 * z.th * (z.units * z.ns + (z.ns + 3) / 4 * 4 * z.mk); }
+
+// The z-first row kernels' configuration (whole_z: the shard holds all of z).
+// Returns false for rows they do not cover.
+bool z_first(const StreamCfg& s, bool whole_z, ZRowCfg* out) {
+  ZRowCfg z;
+  z.th = s.th;
+  const int modes = s.kz / 2 + 1;  // k = 0 .. k_max
+  if (!s.vec || s.th > 2 || modes > 32) return false;
+  z.ntl = modes <= 16 ? 1 : 2;
+  z.ns = static_cast<int>(ceil_div(modes, 4));
+  z.ns = z.ns <= 2 ? 2 : (z.ns <= 4 ? z.ns : (z.ns <= 6 ? 6 : 8));
+  z.mk = s.kt <= 8 ? 1 : 2;
+  z.fold = whole_z && s.nz >= 2 ? 1 : 0;
+  z.np = z.fold ? (s.nz + 1) / 2 : s.nz;
+  z.np2 = z.fold ? s.nz / 2 : 0;
+  z.steps = static_cast<int>(ceil_div(z.np, 4));
+  z.units = static_cast<int>(ceil_div(z.np, 16));
+  z.fmode = z.fold && s.nz % 32 == 0 ? 2 : 1;
+  // z bases in LDS, four workgroups a CU
+  if (z.units * size_t(z.ntl) * 2 * 64 * 16 > 40 * 1024 || z.units * size_t(z.ns) * 64 * 8 > 40 * 1024) return false;
+  *out = z;
+  return true;
+}
 
 bool mul_ok(int64_t a, int64_t b, int64_t* out) {
   if (a < 0 || b < 0) return false;
@@ -260,8 +322,64 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
                     ? 1
                     : 0;
   }
-  dv.w1_bytes = sc.fuse_y ? 0 : w1;
+  // W1 leaves the workspace where the y contraction is always fused: with
+  // N_t % 4 != 0 the plans have W1 whatever their schedule.
+  const bool has_w1 = !sc.fuse_y || sc.nt % 4 != 0;
+  dv.w1_bytes = has_w1 ? w1 : 0;
   dv.ws_bytes = dv.w1_bytes + w2;
+
+  // ---- z-first rows ----
+  // Taken where they need fewer matrix instructions than the t-first kernels;
+  // the forward contracts y in the same launch under the fused forward's
+  // conditions on y (also for K_t > 8, which the t-first fused kernel does not
+  // cover), with the plane in `parts` where the workspace holds the parts.
+  if (ZRowCfg z; z_first(sc, d->n_local[2] == d->n_global[2], &z)) {
+    const int tcost = t_first_cost(sc);
+    z.ncy = fold_y ? 2 : 1;
+    z.kyt = fold_y ? dv.ay_f.kth : dv.ay_f.ktiles;
+    const int mcols = static_cast<int>(nn_y);
+    z.fused_mrow = static_cast<int>(round_up(mcols, 32)) + 16;
+    z.fused_lds_bytes = size_t(dv.ay_f.ktiles) * dv.ay_f.JQ * 2 * 64 * 16 + size_t(16) * z.ncy * z.fused_mrow * 8 +
+                        size_t(z.units) * z.ntl * 2 * 64 * 16;
+    const bool fwd_better = z_first_fwd_cost(z) < tcost;
+    // Separate launches stay where the fused kernel's two waves per SIMD do not
+    // carry the row work: two mode tiles (28 x 24 x 86 x 32, K_z 36: 245 us
+    // separate, 283 fused) or one t group (99 x 90 x 75 x 10: 289, 333); with
+    // one tile and two groups fused was faster (32 x 128 x 128 x 32, K_z 16:
+    // 445 and 324; 42 x 138 x 52 x 32: 147 and 118).  A plan whose workspace
+    // has no W1 (fused t-first kernels otherwise) stays fused.
+    const bool fused = (flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && mcols <= 256 && dv.K[1] <= 32 &&
+                       z.kyt <= (fold_y ? 1 : 2) && z.fused_lds_bytes <= 160 * 1024 &&
+                       bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2));
+    if (fwd_better && fused) {
+      z.fwd = 2;
+      // A workgroup fills a CU (of 256): the parts that leave the fewest slot
+      // groups on the busiest one, the fewest of those within 5%.
+      const int64_t planes = std::max<int64_t>(bc, 1) * d->n_local[0], jq = dv.ay_f.JQ;
+      int64_t best = 0;
+      for (int64_t parts = 1; parts <= jq; ++parts) {
+        const int64_t gpp = ceil_div(jq, parts);
+        if ((parts - 1) * gpp >= jq || size_t(parts) * w2 > dv.ws_bytes) continue;
+        const int64_t cost = ceil_div(planes * parts, 256) * gpp;
+        if (best == 0 || cost * 20 < best * 19) {
+          best = cost;
+          z.parts = static_cast<int>(parts);
+        }
+      }
+    } else if (fwd_better && has_w1) {
+      z.fwd = 1;
+    }
+    z.ifused_lds_bytes = size_t(dv.ay_i.ktiles) * dv.ay_i.JQ * (fold_y ? 2 : 1) * 2 * 64 * 16 +
+                         size_t(16) * z.ncy * z.fused_mrow * 8 + size_t(z.units) * z.ns * 64 * 8;
+    if (z_first_inv_cost(z) < tcost) {
+      if ((flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && mcols <= 256 && z.fold && dv.ay_i.JQ == z.kyt &&
+          z.kyt <= (fold_y ? 1 : 2) && z.ifused_lds_bytes <= 160 * 1024 && bc * d->n_local[0] < (1 << 24))
+        z.inv = 2;
+      else if (has_w1)
+        z.inv = 1;
+    }
+    dv.zr = z;
+  }
 
   // Separate x and y launches fold in four classes (k mod 4, which is the
   // position mod 4 when N % 4 == 0 and k_max is even) when every class fills
@@ -283,6 +401,12 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     }
   }
 
+  // the parts of a plane are further columns of the x contraction
+  if (dv.zr.fwd == 2) {
+    dv.ax_f = axis(static_cast<int>(d->n_local[0]) * dv.zr.parts, static_cast<int>(dv.K[0]), nn_x, dv.ax_f.fold);
+    dv.ax_f.jdup = dv.zr.parts;
+  }
+
   // Two-part (Re, Im) images: the inverse expansions of the expand kernel
   // (fold 2 or 4 within two K steps) and the y images the fused stream
   // kernels read; dtst_inverse_block expands y with the axis kernels even
@@ -293,7 +417,8 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   expand_parts(dv.ax_i);
   expand_parts(dv.ay_i);
   dv.ay_b = dv.ay_i;
-  if (sc.fuse_y) dv.ay_f.parts = dv.ay_i.parts = 2;
+  if (dv.zr.fwd == 2 || (dv.zr.fwd == 0 && sc.fuse_y)) dv.ay_f.parts = 2;
+  if (dv.zr.inv == 2 || (dv.zr.inv == 0 && sc.fuse_y)) dv.ay_i.parts = 2;
 
   // ---- fused inverse z + t expansion and block epilogue ----
   // The same z + t expansion as the split inverse, with z folded into at
@@ -330,12 +455,16 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   };
   const size_t t_img = size_t(sc.th) * 4 * sc.ct * 64;
   const size_t z_img = size_t(sc.ncls) * sc.zt * z_blocks(sc) * 64 * 4;
-  im.t_fwd = take(t_img);
-  im.t_fwd_adjoint_of_inverse = take(t_img);
-  im.z_fwd = take(z_img);
-  im.t_inv = take(t_img);
-  im.t_inv_adjoint_of_forward = take(t_img);
-  im.z_inv = take(z_img);
+  if (!dv.zr.fwd) {  // the z-first kernels have images of their own
+    im.t_fwd = take(t_img);
+    im.t_fwd_adjoint_of_inverse = take(t_img);
+    im.z_fwd = take(z_img);
+  }
+  if (!dv.zr.inv) {
+    im.t_inv = take(t_img);
+    im.t_inv_adjoint_of_forward = take(t_img);
+    im.z_inv = take(z_img);
+  }
   auto axis_img = [](const AxisCfg& a) {
     return size_t(a.ktiles) * a.JQ * axis_image_classes(a) * a.parts * 64 * 4;
   };
@@ -343,9 +472,20 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   im.x_fwd = take(axis_img(dv.ax_f));
   im.y_inv = take(axis_img(dv.ay_i));
   im.x_inv = take(axis_img(dv.ax_i));
-  im.y_blk = sc.fuse_y ? take(axis_img(dv.ay_b)) : im.y_inv;
+  im.y_blk = sc.fuse_y || dv.zr.inv == 2 ? take(axis_img(dv.ay_b)) : im.y_inv;
   im.z_blk = take(size_t(dv.sb.ncls) * dv.sb.zt * z_blocks(dv.sb) * 64 * 4);
   im.t_blk = take(t_img);
+  if (dv.zr.fwd || dv.zr.inv) {
+    const ZRowCfg& z = dv.zr;
+    im.zr_z_fwd = take(size_t(z.units) * z.ntl * 2 * 64 * 4);
+    im.zr_phase = take(size_t(z.ntl) * 64 * 2);
+    im.zr_t_fwd = take(size_t(z.th) * 4 * z.mk * 64);
+    im.zr_t_fwd_adjoint_of_inverse = take(size_t(z.th) * 4 * z.mk * 64);
+    im.zr_z_inv = take(size_t(z.units) * z.ns * 64 * 2);
+    im.zr_phase_inv = take(ceil_div(z.ns, 4) * 64 * 2);
+    im.zr_t_inv = take(size_t(z.th) * 4 * z.mk * 64);
+    im.zr_t_inv_adjoint_of_forward = take(size_t(z.th) * 4 * z.mk * 64);
+  }
   im.total = off;
 
   *out = dv;
@@ -530,6 +670,99 @@ void z_inverse_image(const Derived& dv, float* dst) {
           }
 }
 
+// Images of the z-first row kernels (k_zrow.hip).  Angles are taken at z + 1/2
+// where z folds (2 pi k (2z + 1) / 2N_z), else at the global z.
+//   forward z: float4 entry ((u*NT + n)*2 + part)*64 + lane, component st: Re
+//     (part 0) or Im of exp(-i angle) of mode k = 16n + m at position 16u + 4st + g;
+//   phases: float2 entry n*64 + lane: exp(i pi k / N_z) of k = 16n + m (forward)
+//     or k = 16n + 4(m & 3) + (m >> 2) (inverse) where z folds, else 1;
+//   forward t: entry ((4j + i)*MK + kk)*64 + lane: K index g of step (j, i) is
+//     t = TH (4g + i) + j (lanes past the extent hold its last TH values
+//     again, with zeros), rows M = 4g' + i': with MK = 2 tile kk is part kk of B_t at
+//     k_t = 8(i' >> 1) + 2g' + (i' & 1); with MK = 1 part i' >> 1 at
+//     k_t = 2g' + (i' & 1);
+//   inverse z: float2 entry (zt*NS + s)*64 + lane: cosine and sine of mode
+//     k = 4s + g at position 16zt + m;
+//   inverse t: entry ((h*KG + kg)*2 + e)*64 + lane: C_t = scale conj(B_t) at
+//     k_t = 4kg + g and the t of row m of group h, part e.
+void zrow_images(const Derived& dv, float* base) {
+  const StreamCfg& sc = dv.sc;
+  const ZRowCfg& z = dv.zr;
+  const dtst_desc& d = dv.d;
+  const Images& im = dv.img;
+  const double ntot = double(d.n_global[0]) * d.n_global[1] * d.n_global[2] * d.n_global[3];
+  const int64_t N = d.n_global[2];
+  const int kmax = sc.kz / 2, kg_n = 2 * z.mk;
+  double re, im_;
+  // exp(-i angle) of mode k at position pos
+  auto zval = [&](int k, int pos) {
+    if (k > kmax || pos >= z.np) re = im_ = 0.0;
+    else if (z.fold) twiddle(2 * N, k, 2 * int64_t(pos) + 1, &re, &im_);
+    else twiddle(N, k, d.offset[2] + pos, &re, &im_);
+  };
+  auto put_phase = [&](size_t at, int k) {
+    re = 1.0;
+    im_ = 0.0;
+    if (z.fold) twiddle(2 * N, k, 1, &re, &im_);  // exp(-i pi k / N)
+    base[at] = static_cast<float>(re);
+    base[at + 1] = static_cast<float>(-im_);
+  };
+  for (int lane = 0; lane < 64; ++lane) {
+    const int m = lane & 15, g = lane >> 4;
+    for (int n = 0; n < z.ntl; ++n) {
+      put_phase(im.zr_phase + size_t(n * 64 + lane) * 2, 16 * n + m);
+      for (int u = 0; u < z.units; ++u)
+        for (int st = 0; st < 4; ++st) {
+          zval(16 * n + m, 16 * u + 4 * st + g);
+          float* e = base + im.zr_z_fwd + ((size_t(u * z.ntl + n) * 2) * 64 + lane) * 4 + st;
+          e[0] = static_cast<float>(re);
+          e[64 * 4] = static_cast<float>(im_);
+        }
+    }
+    for (int n = 0; n < ceil_div(z.ns, 4); ++n)
+      put_phase(im.zr_phase_inv + size_t(n * 64 + lane) * 2, 16 * n + 4 * (m & 3) + (m >> 2));
+    for (int zt = 0; zt < z.units; ++zt)
+      for (int s = 0; s < z.ns; ++s) {
+        zval(4 * s + g, 16 * zt + m);
+        float* e = base + im.zr_z_inv + (size_t(zt * z.ns + s) * 64 + lane) * 2;
+        e[0] = static_cast<float>(re);
+        e[1] = static_cast<float>(-im_);
+      }
+    for (int j = 0; j < z.th; ++j)
+      for (int i = 0; i < 4; ++i)
+        for (int kk = 0; kk < z.mk; ++kk) {
+          // lane 4g + i of a row reads t0 .. t0 + TH - 1
+          const int first = z.th * (4 * g + i), t = std::min(first, sc.nt - z.th) + j;
+          const int gr = m >> 2, ir = m & 3;
+          const bool is_re = z.mk == 2 ? kk == 0 : ir < 2;
+          const int kt = z.mk == 2 ? 8 * (ir >> 1) + 2 * gr + (ir & 1) : 2 * gr + (ir & 1);
+          double v = 0.0, w = 0.0;
+          if (kt < sc.kt && t >= first) {
+            bval(d, 3, kt, t, &re, &im_);
+            v = is_re ? re : im_;
+            w = v * (half_weight(d.n_global[3], kt) / ntot);
+          }
+          const size_t o = size_t((4 * j + i) * z.mk + kk) * 64 + lane;
+          base[im.zr_t_fwd + o] = static_cast<float>(v);
+          base[im.zr_t_fwd_adjoint_of_inverse + o] = static_cast<float>(w);
+        }
+    for (int h = 0; h < z.th; ++h)
+      for (int kg = 0; kg < kg_n; ++kg)
+        for (int e = 0; e < 2; ++e) {
+          const int t = t_chunk_start(16 * h + (m & ~3), sc.nt) + (m & 3), kt = 4 * kg + g;
+          double v = 0.0, w = 0.0;
+          if (kt < sc.kt) {
+            bval(d, 3, kt, t, &re, &im_);
+            v = e == 0 ? re : -im_;
+            w = v * (half_weight(d.n_global[3], kt) / ntot);
+          }
+          const size_t o = size_t((h * kg_n + kg) * 2 + e) * 64 + lane;
+          base[im.zr_t_inv + o] = static_cast<float>(w);
+          base[im.zr_t_inv_adjoint_of_forward + o] = static_cast<float>(v);
+        }
+  }
+}
+
 // Axis image, float4 entries indexed by lane (m = lane & 15, g = lane >> 4)
 // and component i.  With 3 parts (the axis kernels) part 0 holds Br, part 1
 // Bi - Br, part 2 Br + Bi of the basis value Br + i Bi; with 2 parts (the y
@@ -545,7 +778,7 @@ void z_inverse_image(const Derived& dv, float* dst) {
 //           p = 4 (16 (kt / 4) + m) + c, column j = 16q + 4g + i < J/4.
 //   fold 4: entry (((kt*JQ + q)*4 + c)*2 + part)*64 + lane = basis[y][p],
 //           y = 16kt + m < KO/4, mode p = 4 (16q + 4g + i) + c.
-// forward: basis[k][j] = B_dim[k][j]; inverse: basis[y][p] = conj(B_dim[p][y]).
+// forward: basis[k][j] = B_dim[k][j / jdup]; inverse: basis[y][p] = conj(B_dim[p][y]).
 void axis_image(const Derived& dv, const AxisCfg& a, int dim, bool inverse, float* dst) {
   const dtst_desc& d = dv.d;
   const int ncls = axis_image_classes(a);
@@ -587,7 +820,7 @@ void axis_image(const Derived& dv, const AxisCfg& a, int dim, bool inverse, floa
                   bval(d, dim, j, k, &re, &im);
                   im = -im;
                 } else {
-                  bval(d, dim, k, j, &re, &im);
+                  bval(d, dim, k, j / a.jdup, &re, &im);
                 }
                 if (a.parts == 3) v = part == 0 ? re : (part == 1 ? im - re : re + im);
                 else v = part == 0 ? re : im;
@@ -600,14 +833,24 @@ void axis_image(const Derived& dv, const AxisCfg& a, int dim, bool inverse, floa
 }  // namespace
 
 void build_images(const Derived& dv, std::vector<float>* blob) {
+  TwiddleTables tables;
+  struct Use {
+    explicit Use(TwiddleTables* t) { g_twiddles = t; }
+    ~Use() { g_twiddles = nullptr; }
+  } use(&tables);
   blob->assign(dv.img.total, 0.0f);
   float* b = blob->data();
-  t_forward_image(dv, false, b + dv.img.t_fwd);
-  t_forward_image(dv, true, b + dv.img.t_fwd_adjoint_of_inverse);
-  z_forward_image(dv, b + dv.img.z_fwd);
-  t_inverse_image(dv, true, b + dv.img.t_inv);
-  t_inverse_image(dv, false, b + dv.img.t_inv_adjoint_of_forward);
-  z_inverse_image(dv, b + dv.img.z_inv);
+  if (!dv.zr.fwd) {
+    t_forward_image(dv, false, b + dv.img.t_fwd);
+    t_forward_image(dv, true, b + dv.img.t_fwd_adjoint_of_inverse);
+    z_forward_image(dv, b + dv.img.z_fwd);
+  }
+  if (!dv.zr.inv) {
+    t_inverse_image(dv, true, b + dv.img.t_inv);
+    t_inverse_image(dv, false, b + dv.img.t_inv_adjoint_of_forward);
+    z_inverse_image(dv, b + dv.img.z_inv);
+  }
+  if (dv.zr.fwd || dv.zr.inv) zrow_images(dv, b);
   axis_image(dv, dv.ay_f, 1, false, b + dv.img.y_fwd);
   axis_image(dv, dv.ax_f, 0, false, b + dv.img.x_fwd);
   axis_image(dv, dv.ay_i, 1, true, b + dv.img.y_inv);
