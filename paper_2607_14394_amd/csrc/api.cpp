@@ -348,7 +348,8 @@ dtst_status dtst_plan_ex(const dtst_desc* d, uint32_t flags, dtst_plan_t* out) {
   if (pe == hipSuccess && p->dv.zr.fwd == 2) pe = dtst::prepare_fwd_zty(&p->dv.zr);
   if (pe == hipSuccess && p->dv.zr.inv == 2) pe = dtst::prepare_inv_yzrow(p->dv.zr, p->dv.sc.nt);
   if (pe == hipSuccess && p->dv.blk &&
-      dtst::prepare_block_zt(p->dv.sb, p->dv.d.c_in, p->dv.d.c_out, &p->dv.grid_blk) != hipSuccess) {
+      (p->dv.blk == 2 ? dtst::prepare_block_row(p->dv.zr, p->dv.d.c_in, p->dv.d.c_out, &p->dv.grid_blk)
+                      : dtst::prepare_block_zt(p->dv.sb, p->dv.d.c_in, p->dv.d.c_out, &p->dv.grid_blk)) != hipSuccess) {
     // the device does not take the fused block kernel at this size: the
     // plan keeps the two launches (dtst_plan_block_info reports it)
     (void)hipGetLastError();
@@ -605,6 +606,10 @@ dtst_status dtst_inverse_block(dtst_plan_t p, const void* yhat, const float* x, 
             [&] { return dtst::launch_axis(dv.ay_b, planes, w2, w1, p->blob + dv.img.y_blk, 0, stream); });
   if (e != hipSuccess) return device_status(e, "y expansion launch");
   e = timed(K_INV_ZT_BLOCK, stream, [&] {
+    if (dv.blk == 2)
+      return dtst::launch_inv_row_block(dv.zr, dv.sc, dv.grid_blk, w1, x, w_bypass, y, B,
+                                        dv.d.n_local[0] * dv.d.n_local[1], dv.d.c_in, co, p->blob + dv.img.zr_t_inv,
+                                        p->blob + dv.img.zr_z_inv, p->blob + dv.img.zr_phase_inv, stream);
     return dtst::launch_inv_zt_block(dv.sb, dv.grid_blk, w1, x, w_bypass, y, B,
                                      dv.d.n_local[0] * dv.d.n_local[1], dv.d.c_in, co, p->blob + dv.img.t_blk,
                                      p->blob + dv.img.z_blk, stream);
@@ -615,7 +620,7 @@ dtst_status dtst_inverse_block(dtst_plan_t p, const void* yhat, const float* x, 
 dtst_status dtst_plan_block_info(dtst_plan_t p, size_t* workspace_bytes, int* fused) {
   DTST_TRY(check_plan(p));
   if (workspace_bytes) *workspace_bytes = p->dv.blk_ws_bytes;
-  if (fused) *fused = p->dv.blk;
+  if (fused) *fused = p->dv.blk != 0;
   return ok();
 }
 

@@ -95,11 +95,11 @@ __device__ __forceinline__ void zexp_plain(const float2* urow, const StreamArgs&
 }
 
 // One lane's chunk of four expanded values into the value buffer: T32 when
-// N_t = 32 is known at compile time (16-byte aligned), else at any 4-byte
-// alignment (two 8-byte LDS stores).
+// N_t = 32 is known at compile time or `al` (N_t % 4 == 0) aligned to 16
+// bytes, else at any 4-byte alignment (two 8-byte LDS stores).
 template <int T32>
-__device__ __forceinline__ void put4(float* dst, const v4f& v) {
-  if constexpr (T32) *reinterpret_cast<v4f*>(dst) = v;
+__device__ __forceinline__ void put4(float* dst, const v4f& v, bool al) {
+  if (T32 || al) *reinterpret_cast<v4f*>(dst) = v;
   else *reinterpret_cast<v4f_u*>(dst) = v;
 }
 
@@ -109,7 +109,7 @@ __device__ __forceinline__ void put4(float* dst, const v4f& v) {
 // them too (the same values to the same place), without a condition.
 template <int CT, int TH, bool ALL, int T32>
 __device__ __forceinline__ void texp_plain(const v4f (&W)[CT], const float (&ta)[TH][CT][4], float* yb, int nt,
-                                           int m, int g) {
+                                           bool al, int m, int g) {
   v4f Y[TH];
 #pragma unroll
   for (int mt = 0; mt < TH; ++mt) Y[mt] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -121,7 +121,7 @@ __device__ __forceinline__ void texp_plain(const v4f (&W)[CT], const float (&ta)
       for (int mt = 0; mt < TH; ++mt) Y[mt] = mfma(ta[mt][ct][i], W[ct][i], Y[mt]);
 #pragma unroll
   for (int mt = 0; mt < TH; ++mt) {
-    if (ALL || t_chunk<TH, 0>(mt, g, nt)) put4<T32>(yb + yoff(m, t_start<TH, 0>(mt, g, nt), nt), Y[mt]);
+    if (ALL || t_chunk<TH, 0>(mt, g, nt)) put4<T32>(yb + yoff(m, t_start<TH, 0>(mt, g, nt), nt), Y[mt], al);
   }
 }
 
@@ -166,7 +166,7 @@ __device__ __forceinline__ void zexp_tfg(const float2* urow, const StreamArgs& a
 // Even / odd k_t t expansion of one class (E + O at t, E - O at t + N_t/2).
 template <int TH, int T32>
 __device__ __forceinline__ void texp_tfg(const v4f& Wr, const v4f& Wi, const float (&ta)[TH][2][4], float* yb, int nt,
-                                         int m, int g) {
+                                         bool al, int m, int g) {
   v4f E[TH / 2], O[TH / 2];
 #pragma unroll
   for (int mt = 0; mt < TH / 2; ++mt) {
@@ -184,8 +184,8 @@ __device__ __forceinline__ void texp_tfg(const v4f& Wr, const v4f& Wi, const flo
 #pragma unroll
   for (int mt = 0; mt < TH / 2; ++mt) {
     const int t0 = t_start<TH, 1>(mt, g, nt);
-    put4<T32>(yb + yoff(m, t0, nt), E[mt] + O[mt]);
-    put4<T32>(yb + yoff(m, t0 + nt / 2, nt), E[mt] - O[mt]);
+    put4<T32>(yb + yoff(m, t0, nt), E[mt] + O[mt], al);
+    put4<T32>(yb + yoff(m, t0 + nt / 2, nt), E[mt] - O[mt], al);
   }
 }
 
@@ -412,6 +412,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
     constexpr int PAR = decltype(parc)::value, HF = decltype(hfc)::value, OHI = decltype(ohc)::value;
     constexpr bool FAST = decltype(fastc)::value;
     float* yb = ybuf + PAR * bufsz;
+    const bool al = !FAST && (nt & 3) == 0;  // (the unconditional passes stay one basic block)
     // (Channel o, slot k of this wave, exists; in the unconditional passes,
     // C_out = 4 KI, this is known at compile time for the slots whose
     // channels all lie below 4 KI.)
@@ -422,7 +423,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
         const int kk = OHI * KCH + k, ol = w + NW * k, o = 16 * OHI + ol;
         if (DTST_BLK_HAS(k, o)) {
           if (HF == 0) zexp_tfg<MT, NCLS>(sbuf + o * spec_len, a, lds, c.zt, m, g, lane, Wzr[kk], Wzi[kk]);
-          texp_tfg<TH, T32>(Wzr[kk][HF], Wzi[kk][HF], ta, yb + ol * ba.ostride, nt, m, g);
+          texp_tfg<TH, T32>(Wzr[kk][HF], Wzi[kk][HF], ta, yb + ol * ba.ostride, nt, al, m, g);
         }
       }
     } else {
@@ -441,7 +442,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
 #pragma unroll
       for (int k = 0; k < KCH; ++k) {
         const int kk = OHI * KCH + k, ol = w + NW * k, o = 16 * OHI + ol;
-        if (DTST_BLK_HAS(k, o)) texp_plain<CT, TH, FAST, T32>(Wz[kk][HF], ta, yb + ol * ba.ostride, nt, m, g);
+        if (DTST_BLK_HAS(k, o)) texp_plain<CT, TH, FAST, T32>(Wz[kk][HF], ta, yb + ol * ba.ostride, nt, al, m, g);
       }
     }
   };

@@ -71,7 +71,7 @@ struct StreamCfg {
 //   ncy, kyt, fused_mrow: as in StreamCfg
 struct ZRowCfg {
   int fwd = 0, inv = 0;
-  int th = 1, fold = 0, ntl = 1, ns = 2, mk = 1;
+  int th = 1, fold = 0, ntl = 1, ns = 0, mk = 1;  // (ns 0: rows the kernels do not cover)
   int np = 0, np2 = 0;
   int steps = 0, units = 0;  // ceil(np / 4), ceil(np / 16)
   int fmode = 1;             // forward: 2 when every position of every unit has its rows (no masks)
@@ -136,7 +136,7 @@ struct Derived {
   // uses it, the workspace it needs (W1 then W2), and its resident grid (set
   // at plan creation on the plan's device).
   StreamCfg sb;
-  int blk = 0;
+  int blk = 0;  // 1: chunked kernel (block_zt.h), 2: row tasks (k_block_row.hip)
   size_t blk_ws_bytes = 0, blk_w1_bytes = 0;
   int grid_blk = 0;
 };
@@ -198,6 +198,13 @@ int prepare_block_zt(const StreamCfg& c, int64_t ci, int64_t co, int* grid);
 int launch_inv_zt_block(const StreamCfg& c, int grid_resident, const void* in, const float* x, const float* w,
                         float* y, int64_t batch, int64_t nxy, int64_t ci, int64_t co, const float* timg,
                         const float* zimg, void* stream);
+// The same for the shapes outside the chunked kernel's unconditional passes
+// (k_block_row.hip), with the images of the z-first inverse.
+bool block_row_supported(const ZRowCfg& c, int64_t ci, int64_t co);
+int prepare_block_row(const ZRowCfg& c, int64_t ci, int64_t co, int* grid);
+int launch_inv_row_block(const ZRowCfg& c, const StreamCfg& s, int grid_resident, const void* in, const float* x,
+                         const float* w, float* y, int64_t batch, int64_t nxy, int64_t ci, int64_t co,
+                         const float* timg, const float* zimg, const float* phase, void* stream);
 int launch_axis(const AxisCfg& c, int64_t nb, const void* in, void* out, const float* img,
                 int accumulate, void* stream);
 // LDS bytes of one workgroup of the mix kernels (mix, mix_h and wgrad alike).

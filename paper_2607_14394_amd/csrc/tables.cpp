@@ -342,15 +342,18 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     z.fused_lds_bytes = size_t(dv.ay_f.ktiles) * dv.ay_f.JQ * 2 * 64 * 16 + size_t(16) * z.ncy * z.fused_mrow * 8 +
                         size_t(z.units) * z.ntl * 2 * 64 * 16;
     const bool fwd_better = z_first_fwd_cost(z) < tcost;
+    const int64_t slots = fold_y ? d->n_local[1] / 2 : d->n_local[1];
     // Separate launches stay where the fused kernel's two waves per SIMD do not
     // carry the row work: two mode tiles (28 x 24 x 86 x 32, K_z 36: 245 us
     // separate, 283 fused) or one t group (99 x 90 x 75 x 10: 289, 333); with
     // one tile and two groups fused was faster (32 x 128 x 128 x 32, K_z 16:
-    // 445 and 324; 42 x 138 x 52 x 32: 147 and 118).  A plan whose workspace
+    // 445 and 324; 42 x 138 x 52 x 32: 147 and 118) unless the last group of
+    // 16 y slots leaves over a quarter of the slots empty (12 x 20 x 108 x 32
+    // with 20 slots: 27 and 29).  A plan whose workspace
     // has no W1 (fused t-first kernels otherwise) stays fused.
     const bool fused = (flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && mcols <= 256 && dv.K[1] <= 32 &&
                        z.kyt <= (fold_y ? 1 : 2) && z.fused_lds_bytes <= 160 * 1024 &&
-                       bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2));
+                       bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2 && slots * 4 >= dv.ay_f.JQ * 16 * 3));
     if (fwd_better && fused) {
       z.fwd = 2;
       // A workgroup fills a CU (of 256): the parts that leave the fewest slot
@@ -440,6 +443,14 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
               block_zt_supported(sb, d->c_in, d->c_out))
                  ? 1
                  : 0;
+    // Row tasks instead of chunks for few input channels, where a chunk's
+    // matrix tiles and waves would mostly idle (chunks -> row tasks, with the
+    // x and y expansions: 5 channels of 3816 rows of 204 x 16: 545 -> 209 us;
+    // 7 of 5940 of 103 x 32: 493 -> 374; 12 of 1232 of 114 x 8: 110 -> 83);
+    // above that the bypass on the vector unit is the slower one (10 channels
+    // of 2184 rows of 42 x 32: 110 -> 136; 16 of 558 of 137 x 8: 88 -> 108).
+    if (dv.blk && (d->c_in <= 8 || (d->c_in <= 12 && sc.th == 1)) && block_row_supported(dv.zr, d->c_in, d->c_out))
+      dv.blk = 2;
     dv.blk_w1_bytes = dv.blk ? w1 : dv.w1_bytes;
     dv.blk_ws_bytes = dv.blk ? w1 + w2 : dv.ws_bytes;
   }
@@ -475,7 +486,7 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   im.y_blk = sc.fuse_y || dv.zr.inv == 2 ? take(axis_img(dv.ay_b)) : im.y_inv;
   im.z_blk = take(size_t(dv.sb.ncls) * dv.sb.zt * z_blocks(dv.sb) * 64 * 4);
   im.t_blk = take(t_img);
-  if (dv.zr.fwd || dv.zr.inv) {
+  if (dv.zr.fwd || dv.zr.inv || dv.blk == 2) {
     const ZRowCfg& z = dv.zr;
     im.zr_z_fwd = take(size_t(z.units) * z.ntl * 2 * 64 * 4);
     im.zr_phase = take(size_t(z.ntl) * 64 * 2);
@@ -850,7 +861,7 @@ void build_images(const Derived& dv, std::vector<float>* blob) {
     t_inverse_image(dv, false, b + dv.img.t_inv_adjoint_of_forward);
     z_inverse_image(dv, b + dv.img.z_inv);
   }
-  if (dv.zr.fwd || dv.zr.inv) zrow_images(dv, b);
+  if (dv.zr.fwd || dv.zr.inv || dv.blk == 2) zrow_images(dv, b);
   axis_image(dv, dv.ay_f, 1, false, b + dv.img.y_fwd);
   axis_image(dv, dv.ax_f, 0, false, b + dv.img.x_fwd);
   axis_image(dv, dv.ay_i, 1, true, b + dv.img.y_inv);

@@ -96,3 +96,32 @@ def test_pointwise_and_epilogue(points):
     check(np_of(y.t), O.block_epilogue(x, w, y0), "block epilogue")
     assert y.guards_intact()
     plan.close()
+
+
+# (n, k_max z, k_t, C_in, C_out, shard): row tasks of few input channels
+ROW_BLOCKS = [((2, 3, 204, 16), 19, 4, 5, 5, None), ((3, 7, 27, 8), 13, 3, 4, 4, None),
+              ((2, 5, 36, 32), 13, 5, 7, 7, None), ((2, 3, 30, 30), 8, 16, 8, 32, None),
+              ((2, 3, 31, 8), 9, 3, 12, 3, None), ((2, 2, 40, 12), 16, 7, 1, 2, (9, 17)), ((5, 61, 2, 6), 1, 2, 3, 1, None),
+              ((9, 40, 50, 32), 6, 9, 2, 5, None)]
+
+
+@pytest.mark.parametrize("case", ROW_BLOCKS, ids=lambda c: "x".join(map(str, c[0])) + f"_c{c[3]}_{c[4]}")
+def test_inverse_block_few_channels(case):
+    """One to three tiles of input channels, one and two mode tiles, ragged and few z positions, a z shard, fewer
+    and more rows than a launch keeps resident."""
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    ng, kz, kt, ci, co, shard = case
+    off, nz = shard if shard else (0, ng[2])
+    n = (ng[0], ng[1], nz, ng[3])
+    g = geometry(ng, n, (0, 0, off, 0), (1, 1, kz), kt, 2, ci, co)
+    say(f"[row block] n={n} kz={kz} kt={kt} c={ci}->{co}")
+    plan = D.Plan(desc_of(g))
+    yh, x = rand_cplx((2, co) + g.K, 55), rand_real((2, ci) + n, 56)
+    wb = (rand_real((co, ci), 57) / np.sqrt(ci)).astype(np.float32)
+    y = Guarded(torch, plan.spatial_shape(co), torch.float32)
+    plan.inverse_block(dev(torch, yh), dev(torch, x), dev(torch, wb), y.t)
+    torch.cuda.synchronize()
+    check(np_of(y.t), O.block_epilogue(x, wb, O.inverse(yh, g)), "inverse + block epilogue")
+    assert y.guards_intact()
+    plan.close()
