@@ -5,6 +5,8 @@
 //   mix_h    g_x[b,i,m]  = sum_o g_y[b,o,m] conj(w[m-m0,i,o])     (data gradient)
 //   wgrad    g_w[m-m0,i,o] (+)= sum_b conj(xhat[b,i,m]) g_y[b,o,m]
 //
+// (row groups of lanes below; C_out <= 64 takes the column forms further down)
+//
 // With B <= 2 the arithmetic intensity is about 1-2 flop/byte, so all three
 // are bound by HBM traffic on w / g_w (M C_in C_out complex values).
 //
@@ -434,6 +436,238 @@ wgrad_kernel(const float2* __restrict__ x, const float2* __restrict__ gy, float2
   }
 }
 
+// ---------------------------------------------------------------------------
+// C_out up to 64: W columns a lane (2, one 16-byte access, for an even C_out and
+// 16-byte aligned w / g_w; else 1).  mix and mix_h give every wave MPW = 64 / CP
+// consecutive modes, CP = C_out / W lanes a mode: with row groups of a power of
+// two lanes 12 of 32 lanes idled at C = 20 (the paper's width), and 8-byte loads
+// kept half as many bytes in flight.  wgrad writes g_w as the flat array it is,
+// 1 KiB a store instruction: rows of 160 bytes (C = 20) end inside 128-byte
+// lines, and a wave writing several of them left lines in parts.
+// 65536 modes, 20 -> 20 channels (210 MB of weights), B = 1, before and now:
+// mix 56.6 -> 46.6 us, mix_h 61.6 -> 44.4, wgrad 81.1 -> 39.9 (5.25 TB/s).
+// ---------------------------------------------------------------------------
+struct PairArgs {
+  int64_t M, m0, count, nblk;
+  int B, ci, co;
+  int cp, mpw, mpb;  // lanes per mode; modes per wave and per workgroup (4 waves)
+};
+
+// Rows [i0, i0 + R) of one mode's matrix, this lane's columns (rows past the
+// end and idle lanes read the first entry and are never used).
+template <int R, int W>
+__device__ __forceinline__ void load_cols(float2 (&v)[R][W], const float2* __restrict__ wm, int i0, int ci, int co,
+                                          int p, bool active) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const int i = i0 + r;
+    const float2* src = wm + (active && i < ci ? i * co + W * p : 0);
+    if constexpr (W == 2) {
+      const float4 t = *reinterpret_cast<const float4*>(src);
+      v[r][0] = make_float2(t.x, t.y);
+      v[r][1] = make_float2(t.z, t.w);
+    } else {
+      v[r][0] = *src;
+    }
+  }
+}
+
+__device__ __forceinline__ void stage_n(float2* dst, const float2* __restrict__ spec, int BC, int64_t M,
+                                        int64_t mbase, int mpb, int nm) {
+  const int per = 256 / mpb, mm = threadIdx.x % mpb, c0 = threadIdx.x / mpb;
+  if (c0 >= per || mm >= nm) return;
+  for (int bc = c0; bc < BC; bc += per) dst[bc * (mpb + 1) + mm] = spec[int64_t(bc) * M + mbase + mm];
+}
+__device__ __forceinline__ void unstage_n(float2* __restrict__ spec, const float2* src, int BC, int64_t M,
+                                          int64_t mbase, int mpb, int nm) {
+  const int per = 256 / mpb, mm = threadIdx.x % mpb, c0 = threadIdx.x / mpb;
+  if (c0 >= per || mm >= nm) return;
+  for (int bc = c0; bc < BC; bc += per) spec[int64_t(bc) * M + mbase + mm] = src[bc * (mpb + 1) + mm];
+}
+
+template <int R, int W>
+__global__ void __launch_bounds__(256)
+mix_cols_kernel(const float2* __restrict__ x, const float2* __restrict__ w, float2* __restrict__ y, PairArgs a) {
+  extern __shared__ float2 sm[];
+  const int st = a.mpb + 1;
+  float2* sx = sm;                    // B * ci rows
+  float2* sy = sm + a.B * a.ci * st;  // B * co rows
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ml = lane / a.cp, p = lane - ml * a.cp, mm = wave * a.mpw + ml;
+  for (int64_t k = first_block(); k < a.nblk; k += gridDim.x) {
+    const int64_t lm0 = k * a.mpb;
+    const int nm = static_cast<int>(min(int64_t(a.mpb), a.count - lm0));
+    const bool active = ml < a.mpw && mm < nm;
+    const float2* wm = w + (lm0 + (active ? mm : 0)) * int64_t(a.ci) * a.co;
+    float2 wv[R][W];
+    load_cols<R, W>(wv, wm, 0, a.ci, a.co, p, active);
+    stage_n(sx, x, a.B * a.ci, a.M, a.m0 + lm0, a.mpb, nm);
+    __syncthreads();
+    for (int i0 = 0; i0 < a.ci; i0 += R) {
+      if (i0 > 0) load_cols<R, W>(wv, wm, i0, a.ci, a.co, p, active);
+      if (!active) continue;
+      for (int b = 0; b < a.B; ++b) {
+        float2 acc[W];
+#pragma unroll
+        for (int c = 0; c < W; ++c) acc[c] = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          if (i0 + r >= a.ci) continue;
+          const float2 xv = sx[(b * a.ci + i0 + r) * st + mm];
+#pragma unroll
+          for (int c = 0; c < W; ++c) {
+            const float2 t = cmul(xv, wv[r][c]);
+            acc[c].x += t.x;
+            acc[c].y += t.y;
+          }
+        }
+        float2* d = sy + (b * a.co + W * p) * st + mm;
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+          if (i0 > 0) {
+            acc[c].x += d[c * st].x;
+            acc[c].y += d[c * st].y;
+          }
+          d[c * st] = acc[c];
+        }
+      }
+    }
+    __syncthreads();
+    unstage_n(y, sy, a.B * a.co, a.M, a.m0 + lm0, a.mpb, nm);
+    __syncthreads();
+  }
+}
+
+// Data gradient: the products of a row over a mode's CP lanes are summed
+// through a wave's own LDS area (no barrier), R rows at a time.
+template <int R, int W>
+__global__ void __launch_bounds__(256)
+mix_h_cols_kernel(const float2* __restrict__ gy, const float2* __restrict__ w, float2* __restrict__ gx, PairArgs a) {
+  extern __shared__ float2 sm[];
+  const int st = a.mpb + 1;
+  float2* sg = sm;                    // B * co rows
+  float2* sx = sm + a.B * a.co * st;  // B * ci rows
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float2* red = sx + a.B * a.ci * st + wave * R * 65;  // R rows of 64 lanes
+  const int ml = lane / a.cp, p = lane - ml * a.cp, mm = wave * a.mpw + ml;
+  for (int64_t k = first_block(); k < a.nblk; k += gridDim.x) {
+    const int64_t lm0 = k * a.mpb;
+    const int nm = static_cast<int>(min(int64_t(a.mpb), a.count - lm0));
+    const bool active = ml < a.mpw && mm < nm;
+    const float2* wm = w + (lm0 + (active ? mm : 0)) * int64_t(a.ci) * a.co;
+    float2 wv[R][W];
+    load_cols<R, W>(wv, wm, 0, a.ci, a.co, p, active);
+    stage_n(sg, gy, a.B * a.co, a.M, a.m0 + lm0, a.mpb, nm);
+    __syncthreads();
+    for (int i0 = 0; i0 < a.ci; i0 += R) {
+      if (i0 > 0) load_cols<R, W>(wv, wm, i0, a.ci, a.co, p, active);
+      const int nr = min(R, a.ci - i0);
+      for (int b = 0; b < a.B; ++b) {
+        float2 gv[W];
+#pragma unroll
+        for (int c = 0; c < W; ++c)
+          gv[c] = active ? sg[(b * a.co + W * p + c) * st + mm] : make_float2(0.f, 0.f);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          float2 t = cjmul(wv[r][0], gv[0]);
+          if constexpr (W == 2) {
+            const float2 t1 = cjmul(wv[r][1], gv[1]);
+            t.x += t1.x;
+            t.y += t1.y;
+          }
+          red[r * 65 + lane] = t;
+        }
+        __builtin_amdgcn_wave_barrier();
+        // sums of (mode, row): lane e of each pass
+        for (int e = lane; e < a.mpw * nr; e += 64) {
+          const int r = e / a.mpw, me = e - r * a.mpw, q = wave * a.mpw + me;
+          float2 t = make_float2(0.f, 0.f);
+          const float2* src = red + r * 65 + me * a.cp;
+          for (int c = 0; c < a.cp; ++c) {
+            const float2 v = src[c];
+            t.x += v.x;
+            t.y += v.y;
+          }
+          if (q < nm) sx[(b * a.ci + i0 + r) * st + q] = t;
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+    __syncthreads();
+    unstage_n(gx, sx, a.B * a.ci, a.M, a.m0 + lm0, a.mpb, nm);
+    __syncthreads();
+  }
+}
+
+// Weight gradient: the block's g_w is one run of W-column elements; thread f of
+// a pass forms columns W p .. of row i of mode mm, f = (mm ci + i) CP + p, from
+// the spectra in LDS ([mode][b][channel]).
+template <int ACC, int W>
+__global__ void __launch_bounds__(256)
+wgrad_flat_kernel(const float2* __restrict__ x, const float2* __restrict__ gy, float2* __restrict__ gw, PairArgs a) {
+  extern __shared__ float4 sm4[];
+  const int sgx = a.B * a.ci + 1, sgy = (a.B * a.co + 3) / 2 * 2;  // mode strides (pairs stay 16-byte aligned)
+  float2* sg = reinterpret_cast<float2*>(sm4);
+  float2* sx = sg + a.mpb * sgy;
+  const int rows = a.ci * a.cp;  // elements of one mode
+  for (int64_t k = first_block(); k < a.nblk; k += gridDim.x) {
+    const int64_t lm0 = k * a.mpb;
+    const int nm = static_cast<int>(min(int64_t(a.mpb), a.count - lm0));
+    const int64_t mbase = a.m0 + lm0;
+    {
+      const int per = 256 / a.mpb, mm = threadIdx.x % a.mpb, c0 = threadIdx.x / a.mpb;
+      if (c0 < per && mm < nm) {
+        for (int c = c0; c < a.B * a.ci; c += per) sx[mm * sgx + c] = x[int64_t(c) * a.M + mbase + mm];
+        for (int c = c0; c < a.B * a.co; c += per) sg[mm * sgy + c] = gy[int64_t(c) * a.M + mbase + mm];
+      }
+    }
+    __syncthreads();
+    float2* out = gw + lm0 * int64_t(a.ci) * a.co;
+    const int n = nm * rows;
+    const int d_row = 256 / a.cp, d_p = 256 - d_row * a.cp;  // a pass further on
+    int row = threadIdx.x / a.cp, p = threadIdx.x - row * a.cp;
+    int mm = row / a.ci, i = row - mm * a.ci;
+    const int d_mm = d_row / a.ci, d_i = d_row - d_mm * a.ci;
+    for (int f = threadIdx.x; f < n; f += 256) {
+      float2 acc[W];
+      if constexpr (ACC && W == 2) {
+        const float4 t = *reinterpret_cast<const float4*>(out + W * f);
+        acc[0] = make_float2(t.x, t.y);
+        acc[W - 1] = make_float2(t.z, t.w);
+      } else {
+#pragma unroll
+        for (int c = 0; c < W; ++c) acc[c] = ACC ? out[W * f + c] : make_float2(0.f, 0.f);
+      }
+      for (int b = 0; b < a.B; ++b) {
+        const float2 xv = sx[mm * sgx + b * a.ci + i];
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+          const float2 t = cjmul(xv, sg[mm * sgy + b * a.co + W * p + c]);
+          acc[c].x += t.x;
+          acc[c].y += t.y;
+        }
+      }
+      if constexpr (W == 2)
+        __builtin_nontemporal_store(v4f{acc[0].x, acc[0].y, acc[1].x, acc[1].y}, reinterpret_cast<v4f*>(out + W * f));
+      else
+        __builtin_nontemporal_store(v2f{acc[0].x, acc[0].y}, reinterpret_cast<v2f*>(out + f));
+      // element f + 256
+      p += d_p;
+      i += d_i;
+      mm += d_mm;
+      if (p >= a.cp) {
+        p -= a.cp;
+        ++i;
+      }
+      if (i >= a.ci) {
+        i -= a.ci;
+        ++mm;
+      }
+    }
+    __syncthreads();
+  }
+}
+
 int lanes_per_row(int64_t co) {
   int l = 1;
   while (l < co && l < 64) l <<= 1;
@@ -570,11 +804,82 @@ struct WgradK2A {
   static constexpr mix_fn fn = wgrad_kernel<L, O, 2, 1>;
 };
 
+// ---- column forms (C_out <= 64) ----
+int cols_of(int64_t co, const void* w) {
+  return co % 2 == 0 && (reinterpret_cast<uintptr_t>(w) & 15) == 0 ? 2 : 1;
+}
+
+PairArgs pair_args(int64_t B, int64_t ci, int64_t co, int64_t M, int64_t m0, int64_t m1, int cols, int mpb) {
+  PairArgs a;
+  a.M = M;
+  a.m0 = m0;
+  a.count = m1 - m0;
+  a.B = static_cast<int>(B);
+  a.ci = static_cast<int>(ci);
+  a.co = static_cast<int>(co);
+  a.cp = static_cast<int>(co / cols);
+  a.mpw = 64 / a.cp;
+  a.mpb = mpb > 0 ? mpb : 4 * a.mpw;
+  a.nblk = (a.count + a.mpb - 1) / a.mpb;
+  return a;
+}
+
+typedef void (*pair_fn)(const float2*, const float2*, float2*, PairArgs);
+
+int launch_pair(pair_fn f, size_t lds, const void* p0, const void* p1, void* p2, const PairArgs& a, void* stream) {
+  if (lds > 65536) {
+    const hipError_t e =
+        hipFuncSetAttribute(reinterpret_cast<const void*>(f), hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  const int64_t cap = int64_t(1) << 22;
+  const int64_t blocks = a.nblk < cap ? a.nblk : cap;
+  hipLaunchKernelGGL(f, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, static_cast<hipStream_t>(stream),
+                     static_cast<const float2*>(p0), static_cast<const float2*>(p1), static_cast<float2*>(p2), a);
+  return hipGetLastError();
+}
+
+// mix and mix_h by row groups of a power of two lanes: rows that fill their
+// groups and are whole 128-byte lines, 16 columns (262144 modes of 16 -> 16, B =
+// 2: mix 127 us and 137 by columns, mix_h 128 and 151) and 32 columns of weights
+// under 1 GB (32768 modes, B = 1: 53 and 57; above, 262144 modes, B = 2: 471 and
+// 448, 484 and 455).
+bool row_groups(int64_t ci, int64_t co, int64_t modes) {
+  return co == 16 || (co == 32 && modes * ci * co * 8 < (int64_t(1) << 30));
+}
+
+// Rows of w in flight: as many as C_in, or the count that leaves the fewest
+// unused ones.
+int rows_in_flight(int64_t ci) {
+  if (ci <= 20) return static_cast<int>((ci + 3) / 4 * 4);
+  int best = 16;
+  for (int r : {20, 12})
+    if ((ci + r - 1) / r * r < (ci + best - 1) / best * best) best = r;
+  return best;
+}
+template <int W>
+pair_fn pick_mix_cols(int r) {
+  return r == 4 ? mix_cols_kernel<4, W> : r == 8 ? mix_cols_kernel<8, W> : r == 12 ? mix_cols_kernel<12, W>
+       : r == 16 ? mix_cols_kernel<16, W> : mix_cols_kernel<20, W>;
+}
+template <int W>
+pair_fn pick_mix_h_cols(int r) {
+  return r == 4 ? mix_h_cols_kernel<4, W> : r == 8 ? mix_h_cols_kernel<8, W> : r == 12 ? mix_h_cols_kernel<12, W>
+       : r == 16 ? mix_h_cols_kernel<16, W> : mix_h_cols_kernel<20, W>;
+}
+
 }  // namespace
 
 int launch_mix(const void* xhat, const void* w, void* yhat, int64_t B, int64_t ci, int64_t co, int64_t M,
                int64_t m0, int64_t m1, void* stream) {
   if (B <= 0 || m1 <= m0) return hipSuccess;
+  if (co <= 64 && !row_groups(ci, co, m1 - m0)) {
+    const int cols = cols_of(co, w), r = rows_in_flight(ci);
+    const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, 0);
+    const size_t lds = sizeof(float2) * size_t(B) * size_t(ci + co) * (a.mpb + 1);
+    if (lds <= 64 * 1024)
+      return launch_pair(cols == 2 ? pick_mix_cols<2>(r) : pick_mix_cols<1>(r), lds, xhat, w, yhat, a, stream);
+  }
   const MixArgs a = make_args(B, ci, co, M, m0, m1, 0);
   return launch(pick<MixK>(co), block_lds(B, ci, co), false, static_cast<const float2*>(xhat),
                 static_cast<const float2*>(w), static_cast<float2*>(yhat), a, stream);
@@ -583,6 +888,16 @@ int launch_mix(const void* xhat, const void* w, void* yhat, int64_t B, int64_t c
 int launch_mix_h(const void* gy, const void* w, void* gx, int64_t B, int64_t ci, int64_t co, int64_t M,
                  int64_t m0, int64_t m1, void* stream) {
   if (B <= 0 || m1 <= m0) return hipSuccess;
+  // (a full wave per row, C_out = 64, sums it in registers faster: 32768 modes
+  // of 12 -> 64, B = 3: 70 us below, 79 us through LDS; of 48 -> 48, B = 2: 165
+  // below, 131 through LDS)
+  if (co < 64 && !row_groups(ci, co, m1 - m0)) {
+    const int cols = cols_of(co, w), r = rows_in_flight(ci);
+    const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, 0);
+    const size_t lds = sizeof(float2) * (size_t(B) * size_t(ci + co) * (a.mpb + 1) + size_t(4) * r * 65);
+    if (lds <= 80 * 1024)
+      return launch_pair(cols == 2 ? pick_mix_h_cols<2>(r) : pick_mix_h_cols<1>(r), lds, gy, w, gx, a, stream);
+  }
   const MixArgs a = make_args(B, ci, co, M, m0, m1, 0);
   return launch(pick<MixHK>(co), block_lds(B, ci, co), false, static_cast<const float2*>(gy),
                 static_cast<const float2*>(w), static_cast<float2*>(gx), a, stream);
@@ -591,6 +906,25 @@ int launch_mix_h(const void* gy, const void* w, void* gx, int64_t B, int64_t ci,
 int launch_wgrad(const void* xhat, const void* gy, void* gw, int64_t B, int64_t ci, int64_t co, int64_t M,
                  int64_t m0, int64_t m1, int accumulate, void* stream) {
   if (B <= 0 || m1 <= m0) return hipSuccess;
+  // Flat g_w, except where rows are whole 128-byte lines and the resident form
+  // below is the faster one: 32 columns (262144 modes of 32 -> 32: 370 us there,
+  // 389 flat); 16 columns of under 1 GB (within a backward step of a 64 x 32 x
+  // 128 x 32 pencil 123 and 126; 4194304 modes alone: 1930 and 1767); and
+  // accumulating 16 or more than 32 (65536 of 16 -> 16: 55 there, 67 flat; 32768
+  // of 48 -> 48, B = 2: 263 and 275).
+  const bool lines = co % 32 == 0 || (accumulate && (co == 16 || co > 32)) ||
+                     (co == 16 && (m1 - m0) * ci * co * 8 < (int64_t(1) << 30));
+  if (co < 64 && !lines) {
+    const int cols = cols_of(co, gw);
+    int mpb = 16;  // modes of a block: at least four passes of the workgroup
+    while (mpb < 64 && mpb * ci * (co / cols) < 1024) mpb *= 2;
+    const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, mpb);
+    const size_t lds = sizeof(float2) * mpb * (size_t(B) * size_t(ci + co) + 4);
+    if (lds <= 64 * 1024)
+      return launch_pair(cols == 2 ? (accumulate ? wgrad_flat_kernel<1, 2> : wgrad_flat_kernel<0, 2>)
+                                   : (accumulate ? wgrad_flat_kernel<1, 1> : wgrad_flat_kernel<0, 1>),
+                         lds, xhat, gy, gw, a, stream);
+  }
   // column pairs (16-byte stores) for an even C_out of at least 4 when g_w
   // is 16-byte aligned and the doubled mode block still fits the LDS
   const size_t lds2 = 2 * block_lds(B, ci, co, co / 2);

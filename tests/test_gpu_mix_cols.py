@@ -1,0 +1,52 @@
+"""Parity of the mix, its data gradient and the weight gradient (overwriting
+and accumulating) at channel counts around the column forms: odd and even
+C_out, wave-filling and ragged lane counts, one to several chunks of rows, the
+widest column form and the row-group form behind it, mode ranges that do not
+fill a block, and guard bands."""
+
+import numpy as np
+import pytest
+
+from gpu_common import Guarded, check, desc_of, dev, geometry, np_of, rand_cplx, say, torch_gpu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [(1, 1, 1), (2, 3, 2), (1, 5, 5), (1, 20, 20), (3, 4, 6), (2, 21, 9), (1, 33, 17), (1, 32, 32), (2, 7, 48),
+         (1, 13, 63), (2, 3, 64), (1, 2, 66)]
+
+
+@pytest.mark.parametrize("b,ci,co", CASES)
+def test_mix_and_gradients(b, ci, co):
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    n = (6, 8, 8, 8)
+    g = geometry(n, n, (0, 0, 0, 0), (2, 3, 3), 3, b, ci, co)
+    plan = D.Plan(desc_of(g))
+    M = plan.n_modes
+    for m0, m1 in ((0, M), (5, 5 + 137), (M - 1, M)):
+        say(f"[mix columns] B={b} {ci}->{co} modes [{m0}, {m1})")
+        x, gy = rand_cplx((b, ci) + g.K, 81), rand_cplx((b, co) + g.K, 82)
+        w, g0 = rand_cplx((m1 - m0, ci, co), 83), rand_cplx((m1 - m0, ci, co), 84)
+        y = Guarded(torch, plan.spectral_shape(co), torch.complex64, fill=torch.zeros(()).cuda())
+        gx = Guarded(torch, plan.spectral_shape(ci), torch.complex64, fill=torch.zeros(()).cuda())
+        gw = Guarded(torch, w.shape, torch.complex64)
+        ga = Guarded(torch, w.shape, torch.complex64, fill=dev(torch, g0))
+        plan.mix(dev(torch, x), dev(torch, w), y.t, m0, m1)
+        plan.mix(dev(torch, gy), dev(torch, w), gx.t, m0, m1, op=1)
+        plan.wgrad(dev(torch, x), dev(torch, gy), gw.t, m0, m1)
+        plan.wgrad(dev(torch, x), dev(torch, gy), ga.t, m0, m1, accumulate=True)
+        torch.cuda.synchronize()
+        xs = x.reshape(b, ci, M)[:, :, m0:m1].astype(np.complex128)
+        gs = gy.reshape(b, co, M)[:, :, m0:m1].astype(np.complex128)
+        wd = w.astype(np.complex128)
+        ref_y, ref_gx = np.zeros((b, co, M), np.complex128), np.zeros((b, ci, M), np.complex128)
+        ref_y[:, :, m0:m1] = np.einsum("bim,mio->bom", xs, wd)
+        ref_gx[:, :, m0:m1] = np.einsum("bom,mio->bim", gs, wd.conj())
+        ref_gw = np.einsum("bim,bom->mio", xs.conj(), gs)
+        check(np_of(y.t).reshape(b, co, M), ref_y, "mix")
+        check(np_of(gx.t).reshape(b, ci, M), ref_gx, "data gradient")
+        check(np_of(gw.t), ref_gw, "weight gradient")
+        check(np_of(ga.t), ref_gw + g0, "weight gradient, accumulated")
+        for t in (y, gx, gw, ga):
+            assert t.guards_intact()
+    plan.close()
