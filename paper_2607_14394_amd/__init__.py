@@ -13,6 +13,12 @@ from __future__ import annotations
 import ctypes
 import os
 
+# torch ships its own HIP runtime under the same soname (libamdhip64.so.7).
+# Loading torch first makes libdtst.so bind to that one copy; loading
+# libdtst.so first would bring a second HIP/HSA runtime into the process,
+# and one of the two then finds no device.
+import torch
+
 __all__ = [
     "DtstError", "Desc", "lib", "make_desc", "dtst_desc_validate", "dtst_desc_workspace_bytes",
     "dtst_basis_host", "dtst_plan", "dtst_plan_destroy", "dtst_plan_info", "dtst_forward", "dtst_mix",
@@ -56,11 +62,6 @@ class Desc(ctypes.Structure):
 
 
 def _load():
-    # torch ships its own HIP runtime under the same soname (libamdhip64.so.7).
-    # Loading torch first makes libdtst.so bind to that one copy; loading
-    # libdtst.so first would bring a second HIP/HSA runtime into the process,
-    # and one of the two then finds no device.
-    import torch  # noqa: F401
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"libdtst.so not found at {LIB_PATH}; build it with "
                           "`python paper_2607_14394_amd/build.py` (no fallback path exists)")
@@ -157,19 +158,24 @@ def dtst_basis_host(desc, dim, kind):
 
 # ---- plans and execute calls (device tensors) ------------------------------
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    # (an integer: the c_void_p argument types convert it)
+    return None if t is None else t.data_ptr()
 
 
 def torch_stream():
     """The current torch stream as the integer value of its hipStream_t."""
-    import torch
+    # torch.cuda.current_stream() builds a Stream object (3 us a call, as much
+    # as a launch); the raw getter returns its handle alone.
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch._C._cuda_getDevice())
     return torch.cuda.current_stream().cuda_stream
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) if hasattr(torch._C, "_cuda_getDevice") else None
+
+
 def _stream(stream):
-    if stream is not None:
-        return ctypes.c_void_p(int(stream))
-    return ctypes.c_void_p(torch_stream())
+    return torch_stream() if stream is None else int(stream)
 
 
 def dtst_plan(desc, flags=0):
@@ -202,7 +208,7 @@ def dtst_plan_block_info(plan):
 def _wsargs(ws):
     if ws is None:
         return None, 0
-    return _ptr(ws), ws.numel() * ws.element_size()
+    return ws.data_ptr(), ws.nbytes
 
 
 def dtst_forward(plan, x, xhat, accumulate, ws, stream=None):
@@ -246,7 +252,6 @@ def dtst_pointwise(x, w, bias, y, act=0, stream=None):
     """y = act(w x + bias) over the points of x (batch, c_in, ...) into y
     (batch, c_out, ...); bias may be None.  Shape checks here, arithmetic in
     the library."""
-    import torch
     if x.dim() < 2 or y.dim() != x.dim() or x.shape[0] != y.shape[0] or x.shape[2:] != y.shape[2:]:
         raise ValueError(f"x {tuple(x.shape)} and y {tuple(y.shape)} must be (batch, channels, points...)")
     for t, name in ((x, "x"), (w, "w"), (y, "y")) + (((bias, "bias"),) if bias is not None else ()):
@@ -283,7 +288,6 @@ class Plan:
     checks on the tensors happen here, the arithmetic in the library."""
 
     def __init__(self, desc, device="cuda", flags=0):
-        import torch
         self.desc = _desc(desc)
         self.handle = dtst_plan(self.desc, flags)
         self.n_modes, self.ws_bytes = dtst_plan_info(self.handle)
@@ -294,6 +298,10 @@ class Plan:
         d = self.desc
         self.K = (2 * d.kmax[0], 2 * d.kmax[1], 2 * d.kmax[2], d.kt)
         self.n_local = tuple(d.n_local)
+        # tensor shapes of the calls (a tuple per call and tensor otherwise)
+        self._x, self._y = self.spatial_shape(d.c_in), self.spatial_shape(d.c_out)
+        self._xhat, self._yhat = self.spectral_shape(d.c_in), self.spectral_shape(d.c_out)
+        self._channels = (d.c_in, d.c_out)
 
     def close(self):
         if self.handle is not None:
@@ -314,61 +322,52 @@ class Plan:
         return (self.desc.batch, channels) + self.K
 
     def _need(self, t, shape, dtype, name):
-        import torch
-        if t.device.type != "cuda":
+        if not t.is_cuda:
             raise ValueError(f"{name} must be a device tensor")
-        if tuple(t.shape) != tuple(shape) or t.dtype != dtype or not t.is_contiguous():
+        if t.shape != shape or t.dtype != dtype or not t.is_contiguous():
             raise ValueError(f"{name}: need contiguous {dtype} of shape {tuple(shape)}, got {t.dtype} {tuple(t.shape)}")
-        return torch
 
     def forward(self, x, xhat, accumulate=False, stream=None):
-        import torch
-        self._need(x, self.spatial_shape(self.desc.c_in), torch.float32, "x")
-        self._need(xhat, self.spectral_shape(self.desc.c_in), torch.complex64, "xhat")
+        self._need(x, self._x, torch.float32, "x")
+        self._need(xhat, self._xhat, torch.complex64, "xhat")
         dtst_forward(self.handle, x, xhat, accumulate, self.ws, stream)
 
     def inverse(self, yhat, y, stream=None):
-        import torch
-        self._need(yhat, self.spectral_shape(self.desc.c_out), torch.complex64, "yhat")
-        self._need(y, self.spatial_shape(self.desc.c_out), torch.float32, "y")
+        self._need(yhat, self._yhat, torch.complex64, "yhat")
+        self._need(y, self._y, torch.float32, "y")
         dtst_inverse(self.handle, yhat, y, self.ws, stream)
 
     def forward_adj(self, g_xhat, g_x, stream=None):
-        import torch
-        self._need(g_xhat, self.spectral_shape(self.desc.c_in), torch.complex64, "g_xhat")
-        self._need(g_x, self.spatial_shape(self.desc.c_in), torch.float32, "g_x")
+        self._need(g_xhat, self._xhat, torch.complex64, "g_xhat")
+        self._need(g_x, self._x, torch.float32, "g_x")
         dtst_forward_adj(self.handle, g_xhat, g_x, self.ws, stream)
 
     def inverse_adj(self, g_y, g_yhat, accumulate=False, stream=None):
-        import torch
-        self._need(g_y, self.spatial_shape(self.desc.c_out), torch.float32, "g_y")
-        self._need(g_yhat, self.spectral_shape(self.desc.c_out), torch.complex64, "g_yhat")
+        self._need(g_y, self._y, torch.float32, "g_y")
+        self._need(g_yhat, self._yhat, torch.complex64, "g_yhat")
         dtst_inverse_adj(self.handle, g_y, g_yhat, accumulate, self.ws, stream)
 
     def mix(self, xhat, w, yhat, m0=0, m1=None, op=0, stream=None):
-        import torch
         m1 = self.n_modes if m1 is None else m1
-        cin, cout = (self.desc.c_in, self.desc.c_out) if op == 0 else (self.desc.c_out, self.desc.c_in)
-        self._need(xhat, self.spectral_shape(cin), torch.complex64, "xhat")
-        self._need(yhat, self.spectral_shape(cout), torch.complex64, "yhat")
-        self._need(w, (m1 - m0, self.desc.c_in, self.desc.c_out), torch.complex64, "w")
+        a, b = (self._xhat, self._yhat) if op == 0 else (self._yhat, self._xhat)
+        self._need(xhat, a, torch.complex64, "xhat")
+        self._need(yhat, b, torch.complex64, "yhat")
+        self._need(w, (m1 - m0,) + self._channels, torch.complex64, "w")
         dtst_mix(self.handle, xhat, w, yhat, m0, m1, op, stream)
 
     def wgrad(self, xhat, g_yhat, g_w, m0=0, m1=None, accumulate=False, stream=None):
-        import torch
         m1 = self.n_modes if m1 is None else m1
-        self._need(xhat, self.spectral_shape(self.desc.c_in), torch.complex64, "xhat")
-        self._need(g_yhat, self.spectral_shape(self.desc.c_out), torch.complex64, "g_yhat")
-        self._need(g_w, (m1 - m0, self.desc.c_in, self.desc.c_out), torch.complex64, "g_w")
+        self._need(xhat, self._xhat, torch.complex64, "xhat")
+        self._need(g_yhat, self._yhat, torch.complex64, "g_yhat")
+        self._need(g_w, (m1 - m0,) + self._channels, torch.complex64, "g_w")
         dtst_mix_wgrad(self.handle, xhat, g_yhat, g_w, m0, m1, accumulate, stream)
 
     def inverse_block(self, yhat, x, w_bypass, y, stream=None):
         """y = GELU(w_bypass x + inverse(yhat)) (the block's last step)."""
-        import torch
-        self._need(yhat, self.spectral_shape(self.desc.c_out), torch.complex64, "yhat")
-        self._need(x, self.spatial_shape(self.desc.c_in), torch.float32, "x")
-        self._need(w_bypass, (self.desc.c_out, self.desc.c_in), torch.float32, "w_bypass")
-        self._need(y, self.spatial_shape(self.desc.c_out), torch.float32, "y")
+        self._need(yhat, self._yhat, torch.complex64, "yhat")
+        self._need(x, self._x, torch.float32, "x")
+        self._need(w_bypass, self._channels[::-1], torch.float32, "w_bypass")
+        self._need(y, self._y, torch.float32, "y")
         ws = self.ws
         if self.block_ws_bytes > self.ws_bytes:
             if self.ws_block is None:
@@ -378,8 +377,7 @@ class Plan:
 
     def block_epilogue(self, x, w_bypass, y, stream=None):
         """y <- GELU(w_bypass x + y) in place (the block's bypass and activation)."""
-        import torch
-        self._need(x, self.spatial_shape(self.desc.c_in), torch.float32, "x")
-        self._need(w_bypass, (self.desc.c_out, self.desc.c_in), torch.float32, "w_bypass")
-        self._need(y, self.spatial_shape(self.desc.c_out), torch.float32, "y")
+        self._need(x, self._x, torch.float32, "x")
+        self._need(w_bypass, self._channels[::-1], torch.float32, "w_bypass")
+        self._need(y, self._y, torch.float32, "y")
         dtst_block_epilogue(self.handle, x, w_bypass, y, stream)
