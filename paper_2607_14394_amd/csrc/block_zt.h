@@ -34,8 +34,9 @@
 //
 // The kernel's instances are compiled in several sources, each of which
 // includes this file: k_block_zt.hip (the launcher; one column tile),
-// k_block_zt1.hip (one column tile, N_t = 32), k_block_zt2.hip (two column
-// tiles), k_block_zt2f.hip (two, t folded).
+// k_block_zt1.hip (one column tile, N_t = 32), k_block_zt1s.hip (one column
+// tile, N_t <= 16), k_block_zt2.hip (two column tiles), k_block_zt2f.hip (two, t
+// folded).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -59,7 +60,7 @@ struct BlockArgs {
   int64_t rows;  // B * N_x * N_y
   int64_t xy;    // N_x * N_y
   int ci, co;
-  int ostride;   // LDS floats per output channel of a buffer: 16 * N_t
+  int ostride;   // LDS floats per output channel of a buffer: 16 ZP N_t
 };
 
 // Float offset of (z row zr, t) in a channel of an LDS value buffer: the
@@ -232,7 +233,13 @@ __device__ __forceinline__ float sum_rows_to_row(float r0, float r1, float r2, f
 // T32 = 1: the instance of N_t = 32 (aligned 16-byte LDS accesses, the swizzled
 // value buffer); 0: every other N_t.  One instance for both, with the choice
 // at run time, held more scalar registers and ran 2% slower at N_t = 32.
-template <int CT, int TH, int MT, int NCLS, int TF, int T32, int KI, int OT, int SPF, int XD, int OH>
+//
+// ZP: z tiles per chunk.  Two t groups fill a chunk of one tile (512 points at
+// N_t = 32, one 64-point group per wave); with N_t <= 16 one tile left half of
+// the waves without points and paid a barrier for half the work (18 channels of
+// 2288 rows of 25 x 8, with the x and y expansions: 100 us, with two tiles 80; 16
+// of 558 of 137 x 8: 89, with four 82; one class only, see z_tiles).
+template <int CT, int TH, int MT, int NCLS, int TF, int T32, int ZP, int KI, int OT, int SPF, int XD, int OH>
 __global__ void __launch_bounds__(64 * kBlkWaves)
 inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, const float* __restrict__ wb,
                     float* __restrict__ y, const float* __restrict__ timg, const float4* __restrict__ zimg,
@@ -259,7 +266,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int m = lane & 15, g = lane >> 4;
-  const int w = tid >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   if (blockIdx.x >= ba.rows) return;  // the host never launches more workgroups than rows
 
   for (int i = tid; i < nimg; i += blockDim.x) lds[i] = zimg[i];
@@ -302,12 +309,14 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
 
   const int64_t row_len = int64_t(a.nz) * a.nt;
   const int nt = T32 ? 32 : a.nt;
-  const int cpr = a.zt * NCLS;  // chunks per row
+  const int czt = (a.zt + ZP - 1) / ZP;  // chunks per row and class
+  const int cpr = czt * NCLS;            // chunks per row
 
   // Channel stride of x and y (floats).
   const int64_t cs = ba.xy * row_len;
 
-  // Chunk position: row, z tile, class; chunks of a row run z tile by z tile.
+  // Chunk position: row, run of ZP z tiles, class; the classes of a run follow
+  // one another.
   // xb, yb: float offsets of channel 0 of the row (b, x, y) in x and y (rows
   // past the end use the last row, whose x the loads past the end re-read).
   struct Cur {
@@ -325,7 +334,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
     c.oh = 0;
     if (++c.hf == NCLS) {
       c.hf = 0;
-      if (++c.zt == a.zt) {
+      if (++c.zt == czt) {
         c.zt = 0;
         c.row += gridDim.x;
         at_row(c);
@@ -350,15 +359,15 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
     int loff;
     bool ok;
   };
-  const bool gok = w * 64 + 4 * m < 16 * nt;
-  const int gpo = min(w * 64 + 4 * m, 16 * nt - 4);
+  const bool gok = w * 64 + 4 * m < 16 * ZP * nt;
+  const int gpo = min(w * 64 + 4 * m, 16 * ZP * nt - 4);
   const int gzr = gpo / nt, gt = gpo - gzr * nt;  // z row and t of the lane's first point in a chunk
   const int gloff = yoff(gzr, gt, nt);
   auto group = [&](const Cur& c) {
     Grp q;
-    const bool zok = c.zt * 16 + gzr < a.zh;
+    const bool zok = c.zt * 16 * ZP + gzr < a.zh;
     q.ok = gok && zok;
-    q.off = zok ? (c.zt * 16 + c.hf * a.zh) * nt + gpo : 0;
+    q.off = (TH == 2 ? zok : q.ok) ? (c.zt * 16 * ZP + c.hf * a.zh) * nt + gpo : 0;
     q.loff = gloff;
     return q;
   };
@@ -401,8 +410,8 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
     for (int k = 0; k < SPF; ++k) reinterpret_cast<v4f*>(sbuf)[min(tid + 64 * NW * k, n4 - 1)] = sp[k];
   };
 
-  // z expansions of this wave's channels, kept for the z tile's chunks
-  v4f Wz[KC][NCLS][CT];              // unfolded t
+  // z expansions of this wave's channels, kept for the other class's chunk
+  v4f Wz[KC][ZP][NCLS][CT];          // unfolded t
   v4f Wzr[KC][NCLS], Wzi[KC][NCLS];  // t folded
 
   // Phase 1 of unit c (chunk class HF, output pass OHI) into buffer PAR:
@@ -422,27 +431,34 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
       for (int k = 0; k < KCH; ++k) {
         const int kk = OHI * KCH + k, ol = w + NW * k, o = 16 * OHI + ol;
         if (DTST_BLK_HAS(k, o)) {
+          static_assert(!TF || ZP == 1, "t folding takes two t groups: one z tile a chunk");
           if (HF == 0) zexp_tfg<MT, NCLS>(sbuf + o * spec_len, a, lds, c.zt, m, g, lane, Wzr[kk], Wzi[kk]);
           texp_tfg<TH, T32>(Wzr[kk][HF], Wzi[kk][HF], ta, yb + ol * ba.ostride, nt, al, m, g);
         }
       }
     } else {
-      if (HF == 0) {
-        float4 Bz[NCLS][MT];
 #pragma unroll
-        for (int cl = 0; cl < NCLS; ++cl)
+      for (int zz = 0; zz < ZP; ++zz) {
+        if constexpr (HF == 0) {
+          // (a run past the last z tile repeats it; its points do not exist)
+          const int zt = ZP == 1 ? c.zt : min(c.zt * ZP + zz, a.zt - 1);
+          float4 Bz[NCLS][MT];
 #pragma unroll
-          for (int q = 0; q < MT; ++q) Bz[cl][q] = lds[((cl * a.zt + c.zt) * MT + q) * 64 + lane];
+          for (int cl = 0; cl < NCLS; ++cl)
+#pragma unroll
+            for (int q = 0; q < MT; ++q) Bz[cl][q] = lds[((cl * a.zt + zt) * MT + q) * 64 + lane];
+#pragma unroll
+          for (int k = 0; k < KCH; ++k) {
+            const int kk = OHI * KCH + k, o = 16 * OHI + w + NW * k;
+            if (DTST_BLK_HAS(k, o)) zexp_plain<CT, MT, NCLS>(sbuf + o * spec_len, a, Bz, m, g, Wz[kk][zz]);
+          }
+        }
 #pragma unroll
         for (int k = 0; k < KCH; ++k) {
-          const int kk = OHI * KCH + k, o = 16 * OHI + w + NW * k;
-          if (DTST_BLK_HAS(k, o)) zexp_plain<CT, MT, NCLS>(sbuf + o * spec_len, a, Bz, m, g, Wz[kk]);
+          const int kk = OHI * KCH + k, ol = w + NW * k, o = 16 * OHI + ol;
+          if (DTST_BLK_HAS(k, o))
+            texp_plain<CT, TH, FAST, T32>(Wz[kk][zz][HF], ta, yb + ol * ba.ostride + 16 * zz * nt, nt, al, m, g);
         }
-      }
-#pragma unroll
-      for (int k = 0; k < KCH; ++k) {
-        const int kk = OHI * KCH + k, ol = w + NW * k, o = 16 * OHI + ol;
-        if (DTST_BLK_HAS(k, o)) texp_plain<CT, TH, FAST, T32>(Wz[kk][HF], ta, yb + ol * ba.ostride, nt, al, m, g);
       }
     }
   };
@@ -624,7 +640,8 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
         phase2_store_full(P2{}, std::integral_constant<int, OH2>{}, c2, C);
         phase1(P1{}, std::integral_constant<int, HF>{}, std::integral_constant<int, OH1>{}, fastc, c1);
       } else {
-        if (has2)
+        // (waves without points leave the SIMD to the ones that share it)
+        if (has2 && w * 64 < 16 * ZP * nt)
           phase2(P2{}, std::integral_constant<int, XB>{}, std::integral_constant<int, OH2>{}, c2);
         if constexpr (LOADS) {
           load_x(XL, cx, fastc);
@@ -635,7 +652,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
     };
     // (c1.hf == HF and c1.oh == OH1 by construction: only the steps whose
     // unit is the last class and pass of a chunk can end a row)
-    if (has1 && HF == NCLS - 1 && OH1 == OH - 1 && c1.zt == a.zt - 1) {
+    if (has1 && HF == NCLS - 1 && OH1 == OH - 1 && c1.zt == czt - 1) {
       // the spectrum loads go out before the step's work, the LDS stores after it
       v4f sp[SPF];
       spec_load(c1.row + gridDim.x, sp);
@@ -705,19 +722,21 @@ const void* kernel_of(F* f) {
   return reinterpret_cast<const void*>(f);
 }
 
-template <int CT, int TH, int MT, int NCLS, int TF, int T32>
+template <int CT, int TH, int MT, int NCLS, int TF, int T32, int ZP>
 const void* pick_kio(int kio) {
-  if (kio == 0) return kernel_of(inv_zt_block_kernel<CT, TH, MT, NCLS, TF, T32, 4, 1, 4, 2, 1>);
-  if (kio == 1) return kernel_of(inv_zt_block_kernel<CT, TH, MT, NCLS, TF, T32, 5, 2, 5, 1, 1>);
-  return kernel_of(inv_zt_block_kernel<CT, TH, MT, NCLS, TF, T32, 8, 1, 8, 2, 2>);
+  if (kio == 0) return kernel_of(inv_zt_block_kernel<CT, TH, MT, NCLS, TF, T32, ZP, 4, 1, 4, 2, 1>);
+  if (kio == 1) return kernel_of(inv_zt_block_kernel<CT, TH, MT, NCLS, TF, T32, ZP, 5, 2, 5, 1, 1>);
+  return kernel_of(inv_zt_block_kernel<CT, TH, MT, NCLS, TF, T32, ZP, 8, 1, 8, 2, 2>);
 }
 
 // Row tiles per class, z classes and (KI, OT) class of an instance with
-// column tiles CT, t groups TH and t folding TF.
-template <int CT, int TH, int TF, int T32>
+// column tiles CT, t groups TH, t folding TF and ZP z tiles per chunk.
+template <int CT, int TH, int TF, int T32, int ZP = 1>
 const void* pick_mn(int mt, int ncls, int kio) {
-  if (mt == 2) return ncls == 2 ? pick_kio<CT, TH, 2, 2, TF, T32>(kio) : pick_kio<CT, TH, 2, 1, TF, T32>(kio);
-  return ncls == 2 ? pick_kio<CT, TH, 4, 2, TF, T32>(kio) : pick_kio<CT, TH, 4, 1, TF, T32>(kio);
+  if constexpr (ZP == 1) {
+    if (ncls == 2) return mt == 2 ? pick_kio<CT, TH, 2, 2, TF, T32, 1>(kio) : pick_kio<CT, TH, 4, 2, TF, T32, 1>(kio);
+  }
+  return mt == 2 ? pick_kio<CT, TH, 2, 1, TF, T32, ZP>(kio) : pick_kio<CT, TH, 4, 1, TF, T32, ZP>(kio);
 }
 
 }  // namespace

@@ -6,7 +6,8 @@ namespace dtst {
 
 // Instances of the other sources.
 const void* block_zt_kernel1(int mt, int ncls, int kio);
-const void* block_zt_kernel2(int th, int t32, int mt, int ncls, int kio);
+const void* block_zt_kernel1s(int zp, int mt, int ncls, int kio);
+const void* block_zt_kernel2(int th, int t32, int zp, int mt, int ncls, int kio);
 const void* block_zt_kernel2f(int t32, int mt, int ncls, int kio);
 
 namespace {
@@ -20,21 +21,36 @@ int kio_of(int64_t ci, int64_t co) {
   return c <= 16 ? 0 : (c <= 20 ? 1 : 2);
 }
 
-const void* pick_blk(const StreamCfg& c, int kio) {
+size_t lds_bytes(const StreamCfg& c, int64_t ci, int64_t co, int zp) {
+  // chunk buffers of 16 channels where the instance makes two output passes
+  const int64_t cb = kio_of(ci, co) == 2 ? 16 : co;
+  return size_t(c.ncls) * c.zt * (c.tf ? 3 * c.mt / 2 : c.mt) * 64 * 16 + size_t(co) * c.kz * c.kt * 8 +
+         2 * size_t(cb) * 16 * zp * c.nt * sizeof(float);
+}
+
+// z tiles per chunk: as many as give the 8 waves points (16 ZP N_t <= 512), the
+// row has and the LDS holds; one with two t groups, and with two z classes (the
+// runs' expansions kept for the second class spilled: 28 channels of 981 rows of
+// 46 x 16 137 -> 147 us).
+int z_tiles(const StreamCfg& c, int64_t ci, int64_t co) {
+  int zp = c.th == 2 || c.nt > 16 || c.ncls == 2 ? 1 : (c.nt > 8 || c.ct == 2 ? 2 : 4);
+  while (zp > 1 && (zp > c.zt || lds_bytes(c, ci, co, zp) > 160 * 1024)) zp /= 2;
+  return zp;
+}
+
+const void* pick_blk(const StreamCfg& c, int64_t ci, int64_t co) {
+  const int kio = kio_of(ci, co), zp = z_tiles(c, ci, co);
   const int t32 = c.nt == 32 ? 1 : 0;
   if (c.tf) return block_zt_kernel2f(t32, c.mt, c.ncls, kio);
-  if (c.ct == 2) return block_zt_kernel2(c.th, t32, c.mt, c.ncls, kio);
-  if (c.th == 1) return pick_mn<1, 1, 0, 0>(c.mt, c.ncls, kio);
+  if (c.ct == 2) return block_zt_kernel2(c.th, t32, zp, c.mt, c.ncls, kio);
+  if (c.th == 1) return block_zt_kernel1s(zp, c.mt, c.ncls, kio);
   return t32 ? block_zt_kernel1(c.mt, c.ncls, kio) : pick_mn<1, 2, 0, 0>(c.mt, c.ncls, kio);
 }
 
 }  // namespace
 
 size_t block_zt_lds_bytes(const StreamCfg& c, int64_t ci, int64_t co) {
-  // chunk buffers of 16 channels where the instance makes two output passes
-  const int64_t cb = kio_of(ci, co) == 2 ? 16 : co;
-  return size_t(c.ncls) * c.zt * (c.tf ? 3 * c.mt / 2 : c.mt) * 64 * 16 + size_t(co) * c.kz * c.kt * 8 +
-         2 * size_t(cb) * 16 * c.nt * sizeof(float);
+  return lds_bytes(c, ci, co, z_tiles(c, ci, co));
 }
 
 // N_t even, and N_z N_t / (z classes) a multiple of 4, which keeps every
@@ -49,7 +65,7 @@ bool block_zt_supported(const StreamCfg& c, int64_t ci, int64_t co) {
 }
 
 int prepare_block_zt(const StreamCfg& c, int64_t ci, int64_t co, int* grid) {
-  const void* fn = pick_blk(c, kio_of(ci, co));
+  const void* fn = pick_blk(c, ci, co);
   const size_t lds = block_zt_lds_bytes(c, ci, co);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
@@ -83,13 +99,13 @@ int launch_inv_zt_block(const StreamCfg& c, int grid_resident, const void* in, c
   ba.xy = nxy;
   ba.ci = static_cast<int>(ci);
   ba.co = static_cast<int>(co);
-  ba.ostride = 16 * c.nt;
+  ba.ostride = 16 * z_tiles(c, ci, co) * c.nt;
   if (c.nt > 4 * kBlkWaves) return hipErrorInvalidConfiguration;  // one 64-point group per wave
   const int64_t grid = rows < grid_resident ? rows : grid_resident;
   const float2* in2 = static_cast<const float2*>(in);
   const float4* zimg4 = reinterpret_cast<const float4*>(zimg);
   void* args[] = {&in2, &x, &w, &y, &timg, &zimg4, &a, &ba};
-  return hipLaunchKernel(pick_blk(c, kio_of(ci, co)), dim3(static_cast<unsigned>(grid)), dim3(64 * kBlkWaves), args,
+  return hipLaunchKernel(pick_blk(c, ci, co), dim3(static_cast<unsigned>(grid)), dim3(64 * kBlkWaves), args,
                          block_zt_lds_bytes(c, ci, co), static_cast<hipStream_t>(stream));
 }
 

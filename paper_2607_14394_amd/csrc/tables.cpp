@@ -342,18 +342,16 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     z.fused_lds_bytes = size_t(dv.ay_f.ktiles) * dv.ay_f.JQ * 2 * 64 * 16 + size_t(16) * z.ncy * z.fused_mrow * 8 +
                         size_t(z.units) * z.ntl * 2 * 64 * 16;
     const bool fwd_better = z_first_fwd_cost(z) < tcost;
-    const int64_t slots = fold_y ? d->n_local[1] / 2 : d->n_local[1];
     // Separate launches stay where the fused kernel's two waves per SIMD do not
     // carry the row work: two mode tiles (28 x 24 x 86 x 32, K_z 36: 245 us
     // separate, 283 fused) or one t group (99 x 90 x 75 x 10: 289, 333); with
     // one tile and two groups fused was faster (32 x 128 x 128 x 32, K_z 16:
-    // 445 and 324; 42 x 138 x 52 x 32: 147 and 118) unless the last group of
-    // 16 y slots leaves over a quarter of the slots empty (12 x 20 x 108 x 32
-    // with 20 slots: 27 and 29).  A plan whose workspace
+    // 445 and 324; 42 x 138 x 52 x 32: 147 and 118; 12 x 20 x 108 x 32: 34 and
+    // 28).  A plan whose workspace
     // has no W1 (fused t-first kernels otherwise) stays fused.
     const bool fused = (flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && mcols <= 256 && dv.K[1] <= 32 &&
                        z.kyt <= (fold_y ? 1 : 2) && z.fused_lds_bytes <= 160 * 1024 &&
-                       bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2 && slots * 4 >= dv.ay_f.JQ * 16 * 3));
+                       bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2));
     if (fwd_better && fused) {
       z.fwd = 2;
       // A workgroup fills a CU (of 256): the parts that leave the fewest slot
