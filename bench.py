@@ -135,18 +135,25 @@ def work(g, channels, m_count=None, acc_share=0.0):
     # t + z + y in one launch: reads the shard once, writes the y-contracted rows
     w["stream_fwd_tzy"] = dict(
         bytes=rows * Nz * Nt * 4 + B * C * Nx * Ky * Kz * Kt * 8,
-        flops=w["stream_fwd_tz"]["flops"] + sf["y"],
-        mfma_flops=w["stream_fwd_tz"]["mfma_flops"] + sf["y"] * fy)
+        flops=w["stream_fwd_tz"]["flops"] + sf["y"])
     spec = B * C * M * 8
     w["axis_fwd_x"] = dict(bytes=B * C * Nx * Ky * Kz * Kt * 8 + spec + acc_share * spec, flops=sf["x"],
                            mfma_flops=sf["x"] * fx * ax)
     w["axis_inv_x"] = dict(bytes=B * C * Nx * Ky * Kz * Kt * 8 + spec, flops=sf["x"], mfma_flops=sf["x"] * fx * ax)
     w["axis_inv_y"] = dict(bytes=w["axis_fwd_y"]["bytes"], flops=sf["y"], mfma_flops=sf["y"] * fy * ax)
-    w["stream_inv_zt"] = dict(bytes=w["stream_fwd_tz"]["bytes"], flops=w["stream_fwd_tz"]["flops"],
-                              mfma_flops=w["stream_fwd_tz"]["mfma_flops"])
+    w["stream_inv_zt"] = dict(w["stream_fwd_tz"])
+    # rows with z contracted first (t expanded first): the real row against cosines and sines of half
+    # the modes (X[-k] is the conjugate of X[k]) over half the z rows, then t by four real products
+    # for both of a pair of modes
+    z_fold = 2 if _folded(g, 2) else 1
+    z_rows = rows * (2 * Kz * Nz * Nt / z_fold + 4 * Kz * Kt * Nt)
+    for role, first in zip(("stream_fwd_tz", "stream_inv_zt"), _z_first(g)):
+        if first:
+            w[role]["mfma_flops"] = z_rows
+    w["stream_fwd_tzy"]["mfma_flops"] = w["stream_fwd_tz"]["mfma_flops"] + sf["y"] * fy
     # y + z + t in one launch: reads the x-expanded spectrum, writes the shard
     w["stream_inv_yzt"] = dict(bytes=w["stream_fwd_tzy"]["bytes"], flops=w["stream_fwd_tzy"]["flops"],
-                               mfma_flops=w["stream_fwd_tzy"]["mfma_flops"])
+                               mfma_flops=w["stream_inv_zt"]["mfma_flops"] + sf["y"] * fy)
     mc = M if m_count is None else m_count
     ci, co = g["c_in"], g["c_out"]
     w["mix"] = dict(bytes=mc * ci * co * 8 + B * (ci + co) * mc * 8, flops=8 * B * mc * ci * co)
@@ -198,11 +205,11 @@ def _axis_classes(g, dim):
 
 
 def _t_classes(g):
-    """2 when the streaming kernels fold t (8 < k_t <= 16 and the whole
-    N_t = 32 local: even k_t from the sums of t and t + N_t/2, odd k_t from
+    """2 when the streaming kernels fold t (8 < k_t <= 16 and the whole even
+    16 < N_t <= 32 local: even k_t from the sums of t and t + N_t/2, odd k_t from
     the differences), else 1; the t MFMA work divides by it."""
     nt = g["n_local"][3]
-    return 2 if 8 < g["kt"] <= 16 and nt == 32 and g["n_global"][3] == nt else 1
+    return 2 if 8 < g["kt"] <= 16 and 16 < nt <= 32 and nt % 2 == 0 and g["n_global"][3] == nt else 1
 
 
 def _z_classes(g):
@@ -230,6 +237,28 @@ def _z_classes(g):
     if four and padded(4) < padded(n):
         n = 4
     return n
+
+
+def _z_first(g):
+    """Whether the stream kernels contract z before t (forward) and expand t
+    before z (inverse): the library's rule, fewer matrix instructions a row
+    than with t first."""
+    Kz, kt, Nz, Nt = 2 * g["kmax"][2], g["kt"], g["n_local"][2], g["n_local"][3]
+    cdiv = lambda a, b: -(-a // b)
+    th, ct, tf, n = cdiv(Nt, 16), 2 if kt > 8 else 1, _t_classes(g) == 2, _z_classes(g)
+    modes = Kz // 2 + 1
+    if Nt < 4 or th > 2 or modes > 32:
+        return False, False
+    slots = 8 if n == 4 and ct == 1 else 16 * cdiv(cdiv(Kz, n), 16)
+    mt = (64 if slots == 48 else slots) // 8
+    t_first = cdiv(cdiv(Nz, n), 16) * n * (th * 4 * ct // (2 if tf else 1) + (3 * mt // 2 if tf else mt * ct) * 4)
+    np_ = cdiv(Nz, 2) if g["n_local"][2] == g["n_global"][2] else Nz
+    ns = max(2, cdiv(modes, 4))
+    ns = ns if ns <= 4 else cdiv(ns, 2) * 2
+    mk = 1 if kt <= 8 else 2
+    fwd = cdiv(modes, 16) * 2 * th * (cdiv(np_, 4) + 4 * mk)
+    inv = 2 * th * (cdiv(np_, 16) * ns + cdiv(ns, 4) * 4 * mk)
+    return fwd < t_first, inv < t_first
 
 
 def _block_z_classes(g):
