@@ -116,8 +116,9 @@ dtst_status dtst_basis_host(const dtst_desc* d, int dim, int kind, float* out, s
  * The plan also fixes the kernel schedule of both chains (dtst_forward and
  * dtst_inverse_adj; dtst_inverse and dtst_forward_adj): where the shapes
  * allow it (K_t <= 8, at most 16 z modes per fold class, 4 <= N_t^loc <= 32,
- * K_y <= 32, K_z K_t <= 256) the t, z and y contractions run as one launch; otherwise t + z and y are separate launches.  Same as
- * dtst_plan_ex(d, 0, out). */
+ * K_y <= 32, K_z K_t <= 256; K_t up to 16 where z is contracted before t) the
+ * t, z and y contractions run as one launch; otherwise t + z and y are
+ * separate launches.  Same as dtst_plan_ex(d, 0, out). */
 dtst_status dtst_plan(const dtst_desc* d, dtst_plan_t* out);
 
 /* Plan options (bit flags of dtst_plan_ex / dtst_desc_workspace_bytes_ex). */
@@ -221,8 +222,8 @@ dtst_status dtst_block_epilogue(dtst_plan_t p, const float* x, const float* w_by
  *   y = GELU( w_bypass x + inverse(yhat) ),
  * with the arrays, layouts, alignment and overlap rules of dtst_inverse and
  * dtst_block_epilogue.  Where the plan allows it (N_t^loc even and at most 32,
- * N_z^loc N_t^loc per z class a multiple of 4, C_in and C_out at most 32, at most 32 z modes per fold class,
- * the per-workgroup buffers within the LDS; see
+ * N_z^loc N_t^loc per z class a multiple of 4, C_in and C_out at most 32, at
+ * most 32 z modes per fold class, the per-workgroup buffers within the LDS; see
  * dtst_plan_block_workspace_bytes) the z and t expansions and the epilogue
  * run as one kernel that writes y once and reads x once; otherwise, or with
  * DTST_PLAN_UNFUSED_BLOCK, the inverse and the epilogue are enqueued one
