@@ -74,6 +74,7 @@ __device__ __forceinline__ float swap_adjacent(float v) {
 struct AxisArgs {
   int64_t nb, total;
   int J, KO, NN, JQ, ktiles, kth, kblocks, nblocks, acc;
+  int ntiles;  // pipelined kernel: a wave's column tiles per (b, k block)
   int jh;  // FOLD 1: J/2 (contracted half); FOLD 2: J/2 (modes per class);
            // FOLD 3: J/4 (contracted quarter); FOLD 4: J/4 (modes per class)
   int oh;  // FOLD 2: KO/2 (output half); FOLD 4: KO/4 (output quarter)
@@ -408,19 +409,22 @@ axis_kernel(const float2* __restrict__ in, float2* __restrict__ out, const float
 }
 
 // Persistent, software-pipelined form of the forward-direction contraction
-// (FOLD 0, 1 or 3, no accumulate) for launches whose basis image fits in
-// LDS.  A grid of resident workgroups walks its work items (b, k block,
-// column block) in order; every wave runs one flat sequence of (item, K
-// step) positions and keeps the input rows of the next PD positions in
-// flight, across item boundaries, so the first steps of an item are loaded
-// while the previous item is still being contracted and written (a work
-// item of a short contraction, J = 64 for instance, is only four K steps:
-// one workgroup per item would expose the input latency at every item
-// start).  The image is copied to LDS once per workgroup; its reads then
-// never wait behind input loads or output stores (global loads and stores
-// share one memory counter per wave, LDS reads do not).  Buffer k holds
-// positions k, k + PD, ...; the loop runs whole passes over the buffers so
-// every buffer index is a compile-time constant.  Loads past the last
+// (FOLD 0, 1 or 3, no accumulate) for launches whose basis image fits in LDS.
+// The waves' entries (b, k block, tile of 16 NT columns) are one flat sequence
+// and a work item is four consecutive ones, so that only a b's last tile can be
+// partly idle: with items of 64 NT columns of one b most waves of every second
+// item had no column at NN = 132 (y of 20 channels of 99 x 90 x 75 x 10, 1980
+// b: 96 us, now 70).  A grid of resident workgroups walks the items in order;
+// every wave runs one flat sequence of (item, K step) positions and keeps the
+// input rows of the next PD positions in flight, across item boundaries, so the
+// first steps of an item are loaded while the previous item is still being
+// contracted and written (a work item of a short contraction, J = 64 for
+// instance, is only four K steps: one workgroup per item would expose the input
+// latency at every item start).  The image is copied to LDS once per workgroup;
+// its reads then never wait behind input loads or output stores (global loads
+// and stores share one memory counter per wave, LDS reads do not).  Buffer k
+// holds positions k, k + PD, ...; the loop runs whole passes over the buffers
+// so every buffer index is a compile-time constant.  Loads past the last
 // position re-read the last item's rows and are never used.
 template <int KT, int NT, int FOLD>
 __global__ void __launch_bounds__(256)
@@ -433,36 +437,36 @@ axis_pipe_kernel(const float2* __restrict__ in, float2* __restrict__ out, const 
   extern __shared__ float4 simg[];
   const int lane = threadIdx.x & 63;
   const int m = lane & 15, g = lane >> 4;
-  const int wave = threadIdx.x >> 6;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t G = gridDim.x;
   const int64_t n_it = a.total > int64_t(blockIdx.x) ? (a.total - 1 - blockIdx.x) / G + 1 : 0;
   if (n_it == 0) return;
   const int lim = FOLD == 0 ? a.J : a.jh;
   const int64_t spare = m < int64_t(a.J) * a.NN ? m : 0;
 
-  // work item `it` of this workgroup -> (b, k block, first column of this
-  // wave); items of one round of the grid are spread over the XCDs in
-  // contiguous logical ranges (as in axis_kernel)
+  // work item `it` of this workgroup -> (b, k block, first column) of this
+  // wave (no columns past the last b); items of one round of the grid are
+  // spread over the XCDs in contiguous logical ranges (as in axis_kernel)
   struct Item {
     int64_t b;
     int kb, nw;
   };
   // (32-bit index arithmetic: the launcher takes this kernel only for fewer
-  // than 2^31 work items)
+  // than 2^31 waves' entries)
   auto item_of = [&](int64_t it) {
     const uint32_t g32 = static_cast<uint32_t>(G), tot = static_cast<uint32_t>(a.total);
     const uint32_t base = static_cast<uint32_t>(it) * g32;
     const uint32_t grid_round = tot - base < g32 ? tot - base : g32;
     const uint32_t per = grid_round / 8, bid = blockIdx.x;
     const uint32_t L = base + (bid >= per * 8 ? bid : (bid % 8) * per + bid / 8);
-    const uint32_t nbl = static_cast<uint32_t>(a.nblocks), kbl = static_cast<uint32_t>(a.kblocks);
+    const uint32_t ntl = static_cast<uint32_t>(a.ntiles), kbl = static_cast<uint32_t>(a.kblocks);
+    const uint32_t e = 4 * L + wave, nb = static_cast<uint32_t>(a.nb);
     Item r;
-    const uint32_t rest = L / nbl;
-    const int nbk = static_cast<int>(L - rest * nbl);
+    const uint32_t rest = e / ntl;
     const uint32_t b = rest / kbl;
     r.kb = static_cast<int>(rest - b * kbl);
-    r.b = b;
-    r.nw = nbk * (64 * NT) + wave * (16 * NT);
+    r.b = b < nb ? b : nb - 1;
+    r.nw = b < nb ? static_cast<int>(e - rest * ntl) * (16 * NT) : a.NN;
     return r;
   };
 
@@ -837,14 +841,12 @@ const void* pipe_fn(int kt, int nt) {
 bool launch_pipe(int fold, int kt, int nt, const AxisCfg& c, AxisArgs a, hipStream_t s, const float2* pin,
                  float2* pout, const float4* pimg, hipError_t* err) {
   const size_t lds = size_t(c.ktiles) * c.JQ * 3 * 64 * sizeof(float4);
-  if (lds > 64 * 1024 || a.nb * a.kblocks * ((c.NN + 63) / 64) >= (int64_t(1) << 31)) return false;
+  if (lds > 64 * 1024 || a.nb * a.kblocks * ((c.NN + 15) / 16) >= (int64_t(1) << 31)) return false;
   // four k tiles keep twelve accumulator tiles per column tile: one column
   // tile per wave (two would leave one wave per SIMD)
   if (kt == 4) nt = 1;
-  if (nt == 1) {
-    a.nblocks = (c.NN + 63) / 64;
-    a.total = a.nb * a.kblocks * a.nblocks;
-  }
+  a.ntiles = (c.NN + 16 * nt - 1) / (16 * nt);
+  a.total = (a.nb * a.kblocks * a.ntiles + 3) / 4;
   const void* f = fold == 0 ? pipe_fn<0>(kt, nt) : (fold == 1 ? pipe_fn<1>(kt, nt) : pipe_fn<3>(kt, nt));
   const int64_t res = resident(f, lds);
   if (res <= 0) {
