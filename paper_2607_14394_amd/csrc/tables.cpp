@@ -241,9 +241,13 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   // t folds (even k_t from x(t) + x(t + N_t/2), odd k_t from the difference)
   // in the split kernels when the shard holds the whole even t extent and
   // each half is one 16-wide group (17 <= N_t <= 32; the kernels read the two
-  // halves at any 4-byte alignment).
+  // halves at any 4-byte alignment).  Its z image is half as large again as
+  // the unfolded one: where only the unfolded one fits the LDS, N_t != 32 stays
+  // unfolded (N_t = 32 always folds).
+  auto z_lds = [&] { return size_t(sc.ncls) * sc.zt * z_blocks(sc) * 64 * 16; };
   sc.tf = (sc.ct == 2 && sc.th == 2 && sc.nt % 2 == 0 && d->n_local[3] == d->n_global[3]) ? 1 : 0;
-  sc.lds_bytes = size_t(sc.ncls) * sc.zt * z_blocks(sc) * 64 * 16;
+  if (sc.nt != 32 && z_lds() > 160 * 1024) sc.tf = 0;
+  sc.lds_bytes = z_lds();
   if (sc.lds_bytes > 160 * 1024) {
     *err = "z basis image exceeds the 160 KiB LDS of a workgroup";
     return DTST_ERR_UNSUPPORTED;

@@ -44,6 +44,18 @@ def test_valid_descriptor():
     D.dtst_desc_validate(desc(n_global=(12, 10, 128, 64), n_local=(4, 10, 128, 64), kmax=(3, 2, 64), kt=16))
 
 
+# Long z at even N_t below 32 and K_t > 8: the folded t image would need half as much LDS again as the unfolded one.
+LONG_Z = [((4, 4, 976, 26), (1, 2, 7), 12), ((2, 12, 1052, 20), (1, 4, 14), 11), ((4, 9, 303, 20), (2, 3, 22), 10),
+          ((6, 4, 232, 18), (2, 2, 52), 10), ((4, 4, 314, 24), (1, 1, 62), 11)]
+
+
+@pytest.mark.parametrize("n,k,kt", LONG_Z)
+def test_long_z_is_accepted(n, k, kt):
+    d = D.make_desc(n, n, (0, 0, 0, 0), k, kt, 1, 2, 2)
+    D.dtst_desc_validate(d)
+    assert D.dtst_desc_workspace_bytes(d) > 0
+
+
 @pytest.mark.parametrize("kw,status", [
     (dict(kmax=(7, 2, 2)), 1),                       # 2k > N
     (dict(kmax=(0, 2, 2)), 1),                       # k = 0

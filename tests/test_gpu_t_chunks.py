@@ -21,14 +21,28 @@ EXTENTS = [(3, 2), (4, 3), (5, 3), (6, 2), (7, 4), (13, 7), (15, 8), (17, 5), (1
 GRIDS = [((3, 4, 32), 5), ((2, 6, 26), 3), ((3, 5, 19), 7)]
 
 
+# Long z whose folded t image would not fit the LDS: t stays unfolded
+LONG_Z = [((2, 3, 976, 26), 7, 12), ((3, 2, 303, 20), 22, 10), ((2, 2, 232, 18), 52, 10), ((2, 2, 314, 24), 62, 11)]
+
+
+@pytest.mark.parametrize("split", [False, True], ids=["default", "split"])
+@pytest.mark.parametrize("n,kz,kt", LONG_Z, ids=lambda v: str(v[2:]) if isinstance(v, tuple) else str(v))
+def test_long_z(n, kz, kt, split):
+    transforms([(n[:3], kz)], n[3], kt, split)
+
+
 @pytest.mark.parametrize("split", [False, True], ids=["default", "split"])
 @pytest.mark.parametrize("nt,kt", EXTENTS)
 def test_transforms(nt, kt, split):
+    transforms(GRIDS, nt, kt, split)
+
+
+def transforms(grids, nt, kt, split):
     torch = torch_gpu()
     import paper_2607_14394_amd as D
-    for (nx, ny, nz), kz in GRIDS:
+    for (nx, ny, nz), kz in grids:
         n = (nx, ny, nz, nt)
-        g = geometry(n, n, (0, 0, 0, 0), (1, 2, kz), kt, 2, 3, 2)
+        g = geometry(n, n, (0, 0, 0, 0), (1, min(2, ny // 2), kz), kt, 2, 3, 2)
         say(f"[t chunks] n={n} kt={kt} kz={kz} split={split}")
         plan = D.Plan(desc_of(g), flags=D.PLAN_SPLIT_SCHEDULE if split else 0)
         x, gy = rand_real((2, 3) + n, 41), rand_real((2, 2) + n, 42)
