@@ -95,9 +95,11 @@ __device__ __forceinline__ void zexp_plain(const float2* urow, const StreamArgs&
   unfold_classes<NCLS, CT>(W);
 }
 
-// One lane's chunk of four expanded values into the value buffer: T32 when
-// N_t = 32 is known at compile time or `al` (N_t % 4 == 0) aligned to 16
-// bytes, else at any 4-byte alignment (two 8-byte LDS stores).
+// One lane's chunk of four expanded values into the value buffer: T32 (N_t = 32
+// known at compile time) or `al` aligned to 16 bytes, else at any 4-byte
+// alignment (two 8-byte LDS stores).  Chunks start at multiples of 4 where N_t
+// is one; t folded, at multiples of 4 of either half where N_t / 2 is one (at
+// N_t = 20 and 28 the second half and the first half's last chunk are not).
 template <int T32>
 __device__ __forceinline__ void put4(float* dst, const v4f& v, bool al) {
   if (T32 || al) *reinterpret_cast<v4f*>(dst) = v;
@@ -421,7 +423,7 @@ inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, 
     constexpr int PAR = decltype(parc)::value, HF = decltype(hfc)::value, OHI = decltype(ohc)::value;
     constexpr bool FAST = decltype(fastc)::value;
     float* yb = ybuf + PAR * bufsz;
-    const bool al = !FAST && (nt & 3) == 0;  // (the unconditional passes stay one basic block)
+    const bool al = !FAST && (nt & (TF ? 7 : 3)) == 0;  // (the unconditional passes stay one basic block)
     // (Channel o, slot k of this wave, exists; in the unconditional passes,
     // C_out = 4 KI, this is known at compile time for the slots whose
     // channels all lie below 4 KI.)

@@ -66,9 +66,11 @@ def transforms(grids, nt, kt, split):
 
 
 @pytest.mark.parametrize("c", [3, 16, 20, 32])
-@pytest.mark.parametrize("nt,kt", [(6, 3), (18, 10), (22, 5), (26, 12), (28, 9), (30, 7), (30, 16)])
+@pytest.mark.parametrize("nt,kt", [(6, 3), (18, 10), (20, 9), (20, 6), (22, 5), (24, 11), (26, 12), (28, 9), (30, 7),
+                                   (30, 16)])
 def test_inverse_block(nt, kt, c):
-    """Even extents: the fused kernel (whole and ragged last z tiles) with each channel class."""
+    """Even extents: the fused kernel (whole and ragged last z tiles) with each channel class; t folded (K_t > 8) with
+    halves that are whole 16-byte chunks (24) and that are not (18, 20, 22, 26, 28, 30)."""
     torch = torch_gpu()
     import paper_2607_14394_amd as D
     for nz, kz in ((32, 5), (26, 3) if nt % 4 == 0 else (20, 3)):
