@@ -100,6 +100,29 @@ dtst_status dtst_desc_workspace_bytes(const dtst_desc* d, size_t* bytes);
 /* The same for a plan made with dtst_plan_ex(d, flags, ...). */
 dtst_status dtst_desc_workspace_bytes_ex(const dtst_desc* d, uint32_t flags, size_t* bytes);
 
+/* The kernels that a plan of this geometry and these flags takes: for tests
+ * and for accounting; results do not depend on it beyond rounding. */
+enum {
+  DTST_ROWS_T_FIRST = 0,   /* rows t then z (inverse: z then t), y a launch of its own */
+  DTST_ROWS_T_FIRST_Y = 1, /* the same with y in the same launch                       */
+  DTST_ROWS_Z_FIRST = 2,   /* rows z then t (inverse: t then z), y a launch of its own */
+  DTST_ROWS_Z_FIRST_Y = 3  /* the same with y in the same launch                       */
+};
+enum {
+  DTST_BLOCK_SEPARATE = 0, /* dtst_inverse_block: the inverse, then the epilogue */
+  DTST_BLOCK_CHUNKS = 1,   /* z + t expansion and epilogue by chunks of a row    */
+  DTST_BLOCK_ROW_TASKS = 2 /* ... by independent tasks (few input channels)      */
+};
+typedef struct {
+  int32_t forward, inverse; /* DTST_ROWS_*: dtst_forward and dtst_inverse_adj; dtst_inverse and dtst_forward_adj */
+  int32_t block;            /* DTST_BLOCK_*: dtst_inverse_block */
+  int32_t z_classes, t_folded;             /* t-first rows: z mode classes (1, 2 or 4), whether t folds */
+  int32_t block_z_classes, block_t_folded; /* the same of DTST_BLOCK_CHUNKS */
+  int32_t z_mirrored;       /* z-first rows: whether rows z and N_z - 1 - z share their products */
+  int32_t y_parts;          /* DTST_ROWS_Z_FIRST_Y forward: parts of a (b, c, x) plane */
+} dtst_schedule;
+dtst_status dtst_desc_schedule(const dtst_desc* d, uint32_t flags, dtst_schedule* out);
+
 /* Write the fp32 basis matrix of dimension `dim` (0..3 = x, y, z, t) that
  * the plan uploads, as an interleaved complex (K_dim x N_dim^loc) host array
  * of `count` floats (count must equal 2*K_dim*N_dim^loc).  kind 0: the

@@ -24,8 +24,8 @@ __all__ = [
     "dtst_basis_host", "dtst_plan", "dtst_plan_destroy", "dtst_plan_info", "dtst_forward", "dtst_mix",
     "dtst_inverse", "dtst_forward_adj", "dtst_inverse_adj", "dtst_mix_wgrad", "dtst_block_epilogue",
     "dtst_inverse_block", "dtst_pointwise", "dtst_forward_noalloc", "dtst_profile_enable",
-    "dtst_profile_collect", "dtst_plan_block_info", "Plan", "LIB_PATH", "PLAN_SPLIT_SCHEDULE",
-    "PLAN_UNFUSED_BLOCK", "SCRATCH_BYTES", "torch_stream",
+    "dtst_profile_collect", "dtst_plan_block_info", "Schedule", "dtst_desc_schedule", "Plan", "LIB_PATH",
+    "PLAN_SPLIT_SCHEDULE", "PLAN_UNFUSED_BLOCK", "SCRATCH_BYTES", "torch_stream",
 ]
 
 LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libdtst.so")
@@ -61,6 +61,18 @@ class Desc(ctypes.Structure):
     ]
 
 
+class Schedule(ctypes.Structure):
+    """dtst_schedule: the kernels a plan takes."""
+    _fields_ = [(n, ctypes.c_int32) for n in
+                ("forward", "inverse", "block", "z_classes", "t_folded", "block_z_classes", "block_t_folded",
+                 "z_mirrored", "y_parts")]
+
+
+# DTST_ROWS_* and DTST_BLOCK_* of include/dtst.h
+ROWS_T_FIRST, ROWS_T_FIRST_Y, ROWS_Z_FIRST, ROWS_Z_FIRST_Y = range(4)
+BLOCK_SEPARATE, BLOCK_CHUNKS, BLOCK_ROW_TASKS = range(3)
+
+
 def _load():
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"libdtst.so not found at {LIB_PATH}; build it with "
@@ -71,6 +83,7 @@ def _load():
         "dtst_desc_validate": [ctypes.POINTER(Desc)],
         "dtst_desc_workspace_bytes": [ctypes.POINTER(Desc), ctypes.POINTER(SZ)],
         "dtst_desc_workspace_bytes_ex": [ctypes.POINTER(Desc), ctypes.c_uint32, ctypes.POINTER(SZ)],
+        "dtst_desc_schedule": [ctypes.POINTER(Desc), ctypes.c_uint32, ctypes.POINTER(Schedule)],
         "dtst_basis_host": [ctypes.POINTER(Desc), I, I, ctypes.POINTER(ctypes.c_float), SZ],
         "dtst_plan": [ctypes.POINTER(Desc), ctypes.POINTER(P)],
         "dtst_plan_ex": [ctypes.POINTER(Desc), ctypes.c_uint32, ctypes.POINTER(P)],
@@ -139,6 +152,12 @@ def dtst_desc_workspace_bytes(desc, flags=0) -> int:
     n = ctypes.c_size_t(0)
     _check(lib.dtst_desc_workspace_bytes_ex(ctypes.byref(_desc(desc)), int(flags), ctypes.byref(n)))
     return n.value
+
+
+def dtst_desc_schedule(desc, flags=0) -> Schedule:
+    s = Schedule()
+    _check(lib.dtst_desc_schedule(ctypes.byref(_desc(desc)), int(flags), ctypes.byref(s)))
+    return s
 
 
 def dtst_basis_host(desc, dim, kind):

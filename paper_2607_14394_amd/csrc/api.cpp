@@ -297,6 +297,29 @@ dtst_status dtst_desc_workspace_bytes(const dtst_desc* d, size_t* bytes) {
   return dtst_desc_workspace_bytes_ex(d, 0, bytes);
 }
 
+dtst_status dtst_desc_schedule(const dtst_desc* d, uint32_t flags, dtst_schedule* out) {
+  if (!out) return fail(DTST_ERR_INVALID_ARG, "out is null");
+  dtst::Derived dv;
+  std::string err;
+  const dtst_status s = dtst::derive(d, flags, &dv, &err);
+  if (s != DTST_OK) return fail(s, err);
+  // (the chains below choose their kernels by the same three fields)
+  auto rows = [&](int z_first) {
+    if (z_first) return z_first == 2 ? DTST_ROWS_Z_FIRST_Y : DTST_ROWS_Z_FIRST;
+    return dv.sc.fuse_y ? DTST_ROWS_T_FIRST_Y : DTST_ROWS_T_FIRST;
+  };
+  out->forward = rows(dv.zr.fwd);
+  out->inverse = rows(dv.zr.inv);
+  out->block = dv.blk == 2 ? DTST_BLOCK_ROW_TASKS : (dv.blk ? DTST_BLOCK_CHUNKS : DTST_BLOCK_SEPARATE);
+  out->z_classes = dv.sc.ncls;
+  out->t_folded = dv.sc.tf;
+  out->block_z_classes = dv.sb.ncls;
+  out->block_t_folded = dv.sb.tf;
+  out->z_mirrored = dv.zr.fold;
+  out->y_parts = dv.zr.parts;
+  return ok();
+}
+
 dtst_status dtst_basis_host(const dtst_desc* d, int dim, int kind, float* out, size_t count) {
   dtst::Derived dv;
   std::string err;

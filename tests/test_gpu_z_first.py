@@ -2,7 +2,9 @@
 both schedules: whole and ragged units and tiles, even and odd whole z and z
 shards, one and two tiles of modes, both k_t tile counts, folded and unfolded
 y with ragged slot groups, planes in parts, t shards, and more rows than a
-launch keeps resident.  Every geometry needs fewer matrix instructions z first."""
+launch keeps resident.  Every geometry of CASES goes z first (asserted from the
+library's schedule); those of T_FIRST are their neighbours that fold t and stay
+t first."""
 
 import pytest
 
@@ -18,16 +20,37 @@ CASES = {
     "whole_units": ((2, 3, 96, 30), (2, 3, 96, 30), (0, 0, 0, 0), (1, 1, 13), 11, 1, 2, 2),
     "two_mode_tiles_kt8": ((2, 3, 101, 32), (2, 3, 101, 32), (0, 0, 0, 0), (1, 1, 16), 8, 1, 1, 1),
     "two_mode_tiles": ((2, 3, 99, 9), (2, 3, 99, 9), (0, 0, 0, 0), (1, 1, 23), 5, 1, 2, 1),
-    "full_spectrum": ((2, 2, 30, 30), (2, 2, 30, 30), (0, 0, 0, 0), (1, 1, 15), 16, 1, 1, 1),
+    "full_spectrum": ((2, 2, 30, 29), (2, 2, 30, 29), (0, 0, 0, 0), (1, 1, 15), 15, 1, 1, 1),
     "one_t_group": ((2, 3, 75, 10), (2, 3, 75, 10), (0, 0, 0, 0), (1, 1, 11), 6, 1, 2, 1),
     "odd_z": ((2, 2, 33, 21), (2, 2, 33, 21), (0, 0, 0, 0), (1, 1, 7), 11, 1, 1, 1),
-    "z_shard": ((2, 2, 64, 32), (2, 2, 23, 32), (0, 0, 17, 0), (1, 1, 8), 16, 1, 1, 2),
+    "z_shard": ((2, 2, 64, 31), (2, 2, 23, 31), (0, 0, 17, 0), (1, 1, 8), 16, 1, 1, 2),
     "t_shard": ((2, 2, 32, 40), (2, 2, 32, 13), (0, 0, 0, 9), (1, 1, 6), 12, 2, 1, 1),
-    "few_z": ((2, 2, 5, 32), (2, 2, 3, 32), (0, 0, 1, 0), (1, 1, 2), 10, 1, 1, 1),
+    "few_z": ((2, 2, 5, 16), (2, 2, 2, 16), (0, 0, 3, 0), (1, 1, 1), 9, 1, 1, 1),
     "y_unfolded_groups": ((3, 37, 40, 32), (3, 37, 40, 32), (0, 0, 0, 0), (1, 9, 5), 9, 1, 2, 1),
     "y_shard": ((3, 80, 40, 30), (3, 40, 40, 30), (0, 11, 0, 0), (1, 16, 4), 16, 1, 1, 2),
     "y_folded_parts": ((4, 112, 48, 32), (2, 112, 48, 32), (1, 0, 0, 0), (2, 8, 6), 16, 1, 2, 3),
     "x_folded_parts": ((8, 96, 64, 30), (8, 96, 64, 30), (0, 0, 0, 0), (3, 4, 7), 10, 1, 1, 1),
+    "many_rows": ((33, 80, 20, 21), (33, 80, 20, 21), (0, 0, 0, 0), (3, 9, 4), 10, 1, 4, 4),
+    # z shards with y in the forward launch: one and two t groups, K_t <= 8 and > 8, y folded, unfolded and a shard,
+    # one and two y tiles, planes in parts (their inverses may stay t first)
+    "zy_shard_one_group": ((16, 29, 56, 16), (16, 29, 41, 16), (0, 0, 0, 0), (2, 11, 4), 8, 1, 1, 2),
+    "zy_shard_y_folded": ((2, 60, 38, 8), (2, 60, 26, 8), (0, 0, 12, 0), (1, 16, 2), 1, 2, 2, 1),
+    "zy_shard_two_groups": ((16, 10, 214, 32), (5, 7, 22, 32), (3, 1, 150, 0), (2, 1, 10), 3, 1, 2, 1),
+    "zy_shard_parts": ((2, 19, 79, 23), (2, 19, 2, 23), (0, 0, 31, 0), (1, 2, 10), 9, 1, 1, 1),
+    "zy_shard_y_folded_parts": ((2, 34, 36, 33), (2, 34, 2, 26), (0, 0, 6, 5), (1, 12, 10), 9, 1, 1, 2),
+    "zy_shard_y_tiles_parts": ((2, 32, 22, 27), (2, 18, 2, 27), (0, 7, 10, 0), (1, 9, 9), 11, 1, 2, 2),
+    "zy_shard_y_folded_parts_kt2": ((2, 34, 61, 31), (2, 34, 2, 17), (0, 0, 9, 0), (1, 7, 10), 2, 1, 1, 1),
+    # z shards of whole rows of 32, two mode tiles, two k_t tiles, the whole z spectrum: y in launches of its own
+    "shard_t32": ((2, 19, 20, 32), (2, 2, 17, 32), (0, 16, 2, 0), (1, 5, 9), 4, 1, 2, 1),
+    "rows_shard_two_tiles": ((2, 65, 38, 32), (2, 65, 36, 32), (0, 0, 2, 0), (1, 4, 19), 7, 1, 1, 2),
+    "rows_shard_kt": ((2, 8, 43, 38), (2, 2, 18, 26), (0, 3, 3, 4), (1, 1, 21), 15, 1, 1, 1),
+    "rows_shard_full": ((2, 2, 62, 29), (2, 2, 22, 19), (0, 0, 29, 7), (1, 1, 31), 15, 1, 1, 1),
+}
+
+T_FIRST = {
+    "full_spectrum": ((2, 2, 30, 30), (2, 2, 30, 30), (0, 0, 0, 0), (1, 1, 15), 16, 1, 1, 1),
+    "z_shard": ((2, 2, 64, 32), (2, 2, 23, 32), (0, 0, 17, 0), (1, 1, 8), 16, 1, 1, 2),
+    "few_z": ((2, 2, 5, 32), (2, 2, 3, 32), (0, 0, 1, 0), (1, 1, 2), 10, 1, 1, 1),
     "many_rows": ((33, 80, 20, 20), (33, 80, 20, 20), (0, 0, 0, 0), (3, 9, 4), 10, 1, 2, 2),
 }
 
@@ -35,11 +58,25 @@ CASES = {
 @pytest.mark.parametrize("split", [False, True], ids=["default", "split"])
 @pytest.mark.parametrize("name", list(CASES))
 def test_z_first(name, split):
+    parity(name, CASES[name], split, z_first=True)
+
+
+@pytest.mark.parametrize("name", list(T_FIRST))
+def test_t_first_neighbours(name):
+    parity(name, T_FIRST[name], False, z_first=False)
+
+
+def parity(name, case, split, z_first):
     torch = torch_gpu()
     import paper_2607_14394_amd as D
-    g = geometry(*CASES[name])
-    say(f"[z first {name}] n_local={g.n_local} kmax={g.kmax} kt={g.kt} split={split}")
-    plan = D.Plan(desc_of(g), flags=D.PLAN_SPLIT_SCHEDULE if split else 0)
+    g = geometry(*case)
+    flags = D.PLAN_SPLIT_SCHEDULE if split else 0
+    s = D.dtst_desc_schedule(desc_of(g), flags)
+    say(f"[z first {name}] n_local={g.n_local} kmax={g.kmax} kt={g.kt} split={split} forward={s.forward} "
+        f"inverse={s.inverse}")
+    for way in (s.forward,) if name.startswith("zy_") else (s.forward, s.inverse):
+        assert (way >= D.ROWS_Z_FIRST) == z_first
+    plan = D.Plan(desc_of(g), flags=flags)
     x, gy = rand_real((g.batch, g.c_in) + g.n_local, 71), rand_real((g.batch, g.c_out) + g.n_local, 72)
     yh, gxh = rand_cplx((g.batch, g.c_out) + g.K, 73), rand_cplx((g.batch, g.c_in) + g.K, 74)
     xhat = Guarded(torch, plan.spectral_shape(g.c_in), torch.complex64)

@@ -1,0 +1,62 @@
+"""The kernels that plans take (dtst_desc_schedule, host only): the parity
+tests' geometries reach the kernels they are meant for."""
+
+import pytest
+
+D = pytest.importorskip("paper_2607_14394_amd", reason="libdtst.so not built")
+
+from test_gpu_t_chunks import ROW_BLOCKS  # noqa: E402
+from test_gpu_z_first import CASES, T_FIRST  # noqa: E402
+
+
+def schedule(case, flags=0):
+    return D.dtst_desc_schedule(D.make_desc(*case), flags)
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_z_first_cases(name):
+    s, split = schedule(CASES[name]), schedule(CASES[name], D.PLAN_SPLIT_SCHEDULE)
+    assert split.forward == D.ROWS_Z_FIRST
+    if name.startswith("zy_"):
+        assert s.forward == D.ROWS_Z_FIRST_Y and not s.z_mirrored
+        assert (s.y_parts > 1) == ("parts" in name)
+        return
+    assert s.forward >= D.ROWS_Z_FIRST and s.inverse >= D.ROWS_Z_FIRST and split.inverse == D.ROWS_Z_FIRST
+    if name.startswith("rows_"):
+        assert s.forward == s.inverse == D.ROWS_Z_FIRST and not s.z_mirrored
+
+
+@pytest.mark.parametrize("name", list(T_FIRST))
+def test_t_first_cases(name):
+    s = schedule(T_FIRST[name])
+    assert s.forward == s.inverse == D.ROWS_T_FIRST and s.t_folded
+
+
+def test_z_first_cases_cover_the_unfolded_fused_forward():
+    """Each (t groups, K_t tiles, y folded) of fwd_zty_kernel without mirrored rows."""
+    seen = set()
+    for c in CASES.values():
+        s = schedule(c)
+        if s.forward == D.ROWS_Z_FIRST_Y and not s.z_mirrored:
+            ng, nl, _, _, kt = c[:5]
+            seen.add((1 if nl[3] <= 16 else 2, 1 if kt <= 8 else 2, nl[1] == ng[1] and ng[1] % 2 == 0))
+    assert seen == {(1, 1, False), (1, 1, True), (2, 1, False), (2, 1, True), (2, 2, False), (2, 2, True)}
+
+
+@pytest.mark.parametrize("case", ROW_BLOCKS, ids=str)
+def test_row_block_cases(case):
+    ng, kz, kt, ci, co, shard = case
+    off, nz = shard if shard else (0, ng[2])
+    s = schedule((ng, (ng[0], ng[1], nz, ng[3]), (0, 0, off, 0), (1, 1, kz), kt, 2, ci, co))
+    assert s.block == D.BLOCK_ROW_TASKS
+
+
+def test_schedule_flags_and_errors():
+    c = ((12, 10, 8, 8), (4, 10, 8, 8), (4, 0, 0, 0), (3, 2, 2), 3, 1, 2, 3)
+    assert schedule(c).forward in (D.ROWS_T_FIRST_Y, D.ROWS_Z_FIRST_Y)
+    assert schedule(c, D.PLAN_SPLIT_SCHEDULE).forward in (D.ROWS_T_FIRST, D.ROWS_Z_FIRST)
+    assert schedule(c, D.PLAN_UNFUSED_BLOCK).block == D.BLOCK_SEPARATE
+    with pytest.raises(D.DtstError):
+        schedule(c, 4)
+    with pytest.raises(D.DtstError):
+        schedule(c[:4] + (17,) + c[5:])
