@@ -438,13 +438,29 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     sb.mt = sb.kcp / 8;
     sb.zh = sb.nz / sb.ncls;
     sb.zt = static_cast<int>(ceil_div(sb.zh, 16));
-    sb.lds_bytes = size_t(sb.ncls) * sb.zt * z_blocks(sb) * 64 * 16;
+    auto fits = [&] {
+      sb.lds_bytes = size_t(sb.ncls) * sb.zt * z_blocks(sb) * 64 * 16;
+      return sb.kcp <= 32 && block_zt_supported(sb, d->c_in, d->c_out);
+    };
     sb.fuse_y = 0;
+    bool fused = fits();
+    // Folding t makes the z image half as large again.  Where only the unfolded
+    // one leaves the kernel its LDS, it runs with t unfolded if its waves are
+    // well filled: one 16-mode tile a class and N_t > 24 with up to 20 channels
+    // (20 channels of 16 x 32 rows of 288 x 28, K_z 16: 340 us in two launches,
+    // 235 fused; 8 x 32 rows of 388 x 28: 205, 183; of 386 x 28 in two classes, 16
+    // channels: 153, 133), or one class and unconditional passes (32 channels of
+    // 480 x 28: 410, 327).  Two launches, with t folded, were faster elsewhere (28
+    // channels of 402 x 28: 304, 316; 16 of 347 x 20, two tiles: 105, 149; 32 of
+    // 384 x 20, two classes: 256, 306).  N_t = 32 is always folded.
+    const int64_t cb = std::max(d->c_in, d->c_out);
+    const bool whole = d->c_in == d->c_out && (cb == 16 || cb == 20 || cb == 32) && sb.zh % 16 == 0;
+    if (!fused && sb.tf && sb.nt != 32 && sb.mt == 2 && ((sb.nt > 24 && cb <= 20) || (whole && sb.ncls == 1))) {
+      sb.tf = 0;
+      fused = fits();
+    }
     dv.sb = sb;
-    dv.blk = ((flags & DTST_PLAN_UNFUSED_BLOCK) == 0 && sb.kcp <= 32 &&
-              block_zt_supported(sb, d->c_in, d->c_out))
-                 ? 1
-                 : 0;
+    dv.blk = (flags & DTST_PLAN_UNFUSED_BLOCK) == 0 && fused ? 1 : 0;
     // Row tasks instead of chunks for few input channels, where a chunk's
     // matrix tiles and waves would mostly idle (chunks -> row tasks, with the
     // x and y expansions: 5 channels of 3816 rows of 204 x 16: 545 -> 209 us;

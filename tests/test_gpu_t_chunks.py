@@ -89,6 +89,27 @@ def test_inverse_block(nt, kt, c):
         plan.close()
 
 
+@pytest.mark.parametrize("n,kz,kt,c", [((2, 3, 288, 28), 8, 15, 20), ((2, 2, 388, 28), 5, 13, 20),
+                                       ((2, 2, 386, 28), 10, 11, 16), ((2, 2, 480, 28), 8, 9, 32)])
+def test_inverse_block_long_z(n, kz, kt, c):
+    """t folds in the transforms and not in the fused block kernel, whose LDS the folded z image would exceed."""
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    g = geometry(n, n, (0, 0, 0, 0), (1, 1, kz), kt, 2, c, c)
+    s = D.dtst_desc_schedule(desc_of(g))
+    assert s.t_folded and s.block == D.BLOCK_CHUNKS and not s.block_t_folded
+    say(f"[t chunks, long block] n={n} kt={kt} c={c}")
+    plan = D.Plan(desc_of(g))
+    yh, x = rand_cplx((2, c) + g.K, 51), rand_real((2, c) + n, 52)
+    wb = (rand_real((c, c), 53) / np.sqrt(c)).astype(np.float32)
+    y = Guarded(torch, plan.spatial_shape(c), torch.float32)
+    plan.inverse_block(dev(torch, yh), dev(torch, x), dev(torch, wb), y.t)
+    torch.cuda.synchronize()
+    check(np_of(y.t), O.block_epilogue(x, wb, O.inverse(yh, g)), "inverse + block epilogue")
+    assert y.guards_intact()
+    plan.close()
+
+
 @pytest.mark.parametrize("points", [1, 3, 4, 5, 6, 7, 1022])
 def test_pointwise_and_epilogue(points):
     """Point counts around the 4-point accesses; in place (epilogue) and out of place (point-wise layer)."""

@@ -51,6 +51,20 @@ def test_row_block_cases(case):
     assert s.block == D.BLOCK_ROW_TASKS
 
 
+# (n, k_max z, k_t, C_in, C_out), fused: blocks whose folded z image leaves the chunked kernel too little LDS
+LONG_BLOCKS = [((2, 3, 288, 28), 8, 15, 20, 20, True), ((2, 2, 388, 28), 5, 13, 20, 20, True),
+               ((2, 2, 386, 28), 10, 11, 16, 16, True), ((2, 2, 480, 28), 8, 9, 32, 32, True),
+               ((2, 2, 402, 28), 7, 9, 28, 28, False), ((2, 2, 347, 20), 11, 11, 16, 16, False)]
+
+
+@pytest.mark.parametrize("case", LONG_BLOCKS, ids=str)
+def test_long_blocks_keep_the_fused_kernel_unfolded(case):
+    n, kz, kt, ci, co, fused = case
+    s = schedule((n, n, (0, 0, 0, 0), (1, 1, kz), kt, 2, ci, co))
+    assert s.t_folded
+    assert (s.block, s.block_t_folded) == ((D.BLOCK_CHUNKS, 0) if fused else (D.BLOCK_SEPARATE, 1))
+
+
 def test_schedule_flags_and_errors():
     c = ((12, 10, 8, 8), (4, 10, 8, 8), (4, 0, 0, 0), (3, 2, 2), 3, 1, 2, 3)
     assert schedule(c).forward in (D.ROWS_T_FIRST_Y, D.ROWS_Z_FIRST_Y)
