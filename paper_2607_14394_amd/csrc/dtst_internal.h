@@ -169,6 +169,10 @@ int launch_fwd_tzy(const StreamCfg& c, const AxisCfg& ay, const float* x, void* 
 // image (yimg) supplies the y basis.
 int launch_inv_yzt(const StreamCfg& c, const AxisCfg& ay, const void* in, float* y, int64_t planes, int ny,
                    const float* timg, const float* zimg, const float* yimg, void* stream);
+// The fused inverses launch one workgroup of 1024 threads per plane (or part of
+// one) and a launch holds fewer than 2^32 threads in a dimension: planes beyond
+// this many go in further launches.
+constexpr int64_t kInvPlanesPerLaunch = int64_t(1) << 21;
 int launch_inv_zt(const StreamCfg& c, const void* in, float* y, int64_t rows,
                   const float* timg, const float* zimg, void* stream);
 // The z-first row kernels (k_zrow.hip): forward rows into (rows x K_z K_t)

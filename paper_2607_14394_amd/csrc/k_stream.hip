@@ -20,6 +20,7 @@
 // without any data movement.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dtst_internal.h"
@@ -1413,7 +1414,6 @@ int launch_inv_yzt(const StreamCfg& c, const AxisCfg& ay, const void* in, float*
   // The y expansion's image must have the K steps and tiles the kernel assumes.
   if (ay.JQ != c.kyt || (ay.fold == 2) != (c.ncy == 2)) return hipErrorInvalidValue;
   FusedArgs f;
-  f.planes = planes;
   f.ny = ny;
   f.slots = ay.fold == 2 ? ny / 2 : ny;
   f.half = ay.fold == 2 ? ny / 2 : 0;
@@ -1424,12 +1424,16 @@ int launch_inv_yzt(const StreamCfg& c, const AxisCfg& ay, const void* in, float*
   f.mrow = c.fused_mrow;
   f.nwy = (f.mcols + 15) / 16;
   f.yimg_n4 = ay.ktiles * ay.JQ * (ay.fold == 2 ? 2 : 1) * 2 * 64;
-  if (planes > int64_t(0x7fffffff)) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(pick_ifused(c), dim3(static_cast<unsigned>(planes)), dim3(1024), c.fused_lds_bytes,
-                     static_cast<hipStream_t>(stream), static_cast<const float2*>(in), y, timg,
-                     reinterpret_cast<const float4*>(zimg), reinterpret_cast<const float4*>(yimg),
-                     args_of(c, planes * ny), f);
-  return hipGetLastError();
+  for (int64_t p0 = 0; p0 < planes; p0 += kInvPlanesPerLaunch) {
+    f.planes = std::min(planes - p0, kInvPlanesPerLaunch);
+    hipLaunchKernelGGL(pick_ifused(c), dim3(static_cast<unsigned>(f.planes)), dim3(1024), c.fused_lds_bytes,
+                       static_cast<hipStream_t>(stream), static_cast<const float2*>(in) + p0 * f.ky * f.mcols,
+                       y + p0 * ny * c.nz * c.nt, timg, reinterpret_cast<const float4*>(zimg),
+                       reinterpret_cast<const float4*>(yimg), args_of(c, f.planes * ny), f);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dtst

@@ -11,6 +11,7 @@
 // separate launches the (N_y x K_z K_t) intermediate stays out of HBM.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dtst_internal.h"
@@ -169,7 +170,6 @@ int launch_inv_yzrow(const ZRowCfg& c, const StreamCfg& s, const AxisCfg& ay, co
   // the image must have the K steps and tiles the kernel assumes
   if (ay.JQ != c.kyt || (ay.fold == 2) != (c.ncy == 2) || ay.parts != 2) return hipErrorInvalidValue;
   ZRowArgs a;
-  a.rows = planes * ny;
   a.nt = s.nt;
   a.nz = s.nz;
   a.kt = s.kt;
@@ -196,21 +196,27 @@ int launch_inv_yzrow(const ZRowCfg& c, const StreamCfg& s, const AxisCfg& ay, co
       f.gpp = static_cast<int>(gpp);
     }
   }
-  f.parts = (f.jq + f.gpp - 1) / f.gpp;
-  if (planes * f.parts > 0x7fffffff) return hipErrorInvalidConfiguration;
-  f.items = static_cast<int>(planes) * f.parts;
+  f.parts = (f.jq + f.gpp - 1) / f.gpp;  // (1 where there are more planes than kInvPlanesPerLaunch)
   f.kth = 0;
   f.ky = ay.J;
   f.mcols = s.kz * s.kt;
   f.mrow = c.fused_mrow;
   f.yimg_n4 = ay.ktiles * ay.JQ * (ay.fold == 2 ? 2 : 1) * 2 * 64;
-  const float2* i = static_cast<const float2*>(in);
   const float2* z = reinterpret_cast<const float2*>(zimg);
   const float2* p = reinterpret_cast<const float2*>(phase);
   const float4* yi = reinterpret_cast<const float4*>(yimg);
-  void* args[] = {&i, &y, &z, &p, &timg, &yi, &a, &f};
-  return hipLaunchKernel(pick(c, s.nt), dim3(f.items), dim3(1024), args, c.ifused_lds_bytes,
-                         static_cast<hipStream_t>(stream));
+  for (int64_t p0 = 0; p0 < planes; p0 += kInvPlanesPerLaunch) {
+    const int64_t n = std::min(planes - p0, kInvPlanesPerLaunch);
+    const float2* i = static_cast<const float2*>(in) + p0 * f.ky * f.mcols;
+    float* yp = y + p0 * ny * s.nz * s.nt;
+    a.rows = n * ny;
+    f.items = static_cast<int>(n) * f.parts;
+    void* args[] = {&i, &yp, &z, &p, &timg, &yi, &a, &f};
+    const hipError_t e = hipLaunchKernel(pick(c, s.nt), dim3(f.items), dim3(1024), args, c.ifused_lds_bytes,
+                                         static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dtst
