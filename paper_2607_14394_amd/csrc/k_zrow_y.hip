@@ -229,13 +229,11 @@ const void* pick_fold(const ZRowCfg& c) {
   if (!c.fold) return pick_y<TH, NT, MK, 0, 1>(c.ncy, c.kyt);
   return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2>(c.ncy, c.kyt) : pick_y<TH, NT, MK, 1, 1>(c.ncy, c.kyt);
 }
-template <int TH, int NT>
-const void* pick_mk(const ZRowCfg& c) {
-  return c.mk == 1 ? pick_fold<TH, NT, 1>(c) : pick_fold<TH, NT, 2>(c);
-}
+// The combinations that plans take (zty_covers in tables.cpp): two t groups
+// with one mode tile, one t group with K_t <= 8.
 const void* pick(const ZRowCfg& c) {
-  if (c.th == 2) return c.ntl == 1 ? pick_mk<2, 1>(c) : pick_mk<2, 2>(c);
-  return c.ntl == 1 ? pick_mk<1, 1>(c) : pick_mk<1, 2>(c);
+  if (c.th == 2) return c.mk == 1 ? pick_fold<2, 1, 1>(c) : pick_fold<2, 1, 2>(c);
+  return c.ntl == 1 ? pick_fold<1, 1, 1>(c) : pick_fold<1, 2, 1>(c);
 }
 
 }  // namespace

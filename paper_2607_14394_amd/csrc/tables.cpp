@@ -353,7 +353,8 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     // 445 and 324; 42 x 138 x 52 x 32: 147 and 118; 12 x 20 x 108 x 32: 34 and
     // 28).  A plan whose workspace
     // has no W1 (fused t-first kernels otherwise) stays fused.
-    const bool fused = (flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && mcols <= 256 && dv.K[1] <= 32 &&
+    const bool zty_covers = z.th == 2 ? z.ntl == 1 : z.mk == 1;  // (the instances there are)
+    const bool fused = (flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && zty_covers && mcols <= 256 && dv.K[1] <= 32 &&
                        z.kyt <= (fold_y ? 1 : 2) && z.fused_lds_bytes <= 160 * 1024 &&
                        bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2));
     if (fwd_better && fused) {
