@@ -238,7 +238,7 @@ hipError_t resident(const void* fn, size_t lds, int* grid) {
 int prepare_zrow(ZRowCfg* c, int nt) {
   hipError_t e = hipSuccess;
   if (c->fwd == 1) e = resident(pick_f(*c), lds_fwd(*c), &c->grid_fwd);
-  if (e == hipSuccess && c->inv) e = resident(pick_i(*c, nt), lds_inv(*c), &c->grid_inv);
+  if (e == hipSuccess && c->inv == 1) e = resident(pick_i(*c, nt), lds_inv(*c), &c->grid_inv);
   return e;
 }
 
