@@ -5,7 +5,10 @@
 //   mix_h    g_x[b,i,m]  = sum_o g_y[b,o,m] conj(w[m-m0,i,o])     (data gradient)
 //   wgrad    g_w[m-m0,i,o] (+)= sum_b conj(xhat[b,i,m]) g_y[b,o,m]
 //
-// (row groups of lanes below; C_out <= 64 takes the column forms further down)
+// Row groups of lanes below; the column forms further down take C_out up to 64
+// (mix) or 63 (mix_h, wgrad) except at 16, and mostly 32, columns, where the row
+// groups measured faster (row_groups, and `lines` in launch_wgrad), and where
+// their LDS does not fit.
 //
 // With B <= 2 the arithmetic intensity is about 1-2 flop/byte, so all three
 // are bound by HBM traffic on w / g_w (M C_in C_out complex values).
@@ -538,8 +541,16 @@ mix_cols_kernel(const float2* __restrict__ x, const float2* __restrict__ w, floa
   }
 }
 
+// Orders a wave's LDS accesses before this point with those of its other lanes
+// after it (no instruction on this hardware: a wave's LDS accesses stay in order).
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Data gradient: the products of a row over a mode's CP lanes are summed
-// through a wave's own LDS area (no barrier), R rows at a time.
+// through a wave's own LDS area (no workgroup barrier), R rows at a time.
 template <int R, int W>
 __global__ void __launch_bounds__(256)
 mix_h_cols_kernel(const float2* __restrict__ gy, const float2* __restrict__ w, float2* __restrict__ gx, PairArgs a) {
@@ -577,7 +588,7 @@ mix_h_cols_kernel(const float2* __restrict__ gy, const float2* __restrict__ w, f
           }
           red[r * 65 + lane] = t;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
         // sums of (mode, row): lane e of each pass
         for (int e = lane; e < a.mpw * nr; e += 64) {
           const int r = e / a.mpw, me = e - r * a.mpw, q = wave * a.mpw + me;
@@ -590,7 +601,7 @@ mix_h_cols_kernel(const float2* __restrict__ gy, const float2* __restrict__ w, f
           }
           if (q < nm) sx[(b * a.ci + i0 + r) * st + q] = t;
         }
-        __builtin_amdgcn_wave_barrier();
+        wave_sync();
       }
     }
     __syncthreads();
