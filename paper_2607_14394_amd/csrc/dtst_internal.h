@@ -74,6 +74,7 @@ struct ZRowCfg {
   int th = 1, fold = 0, ntl = 1, ns = 0, mk = 1;  // (ns 0: rows the kernels do not cover)
   int np = 0, np2 = 0;
   int steps = 0, units = 0;  // ceil(np / 4), ceil(np / 16)
+  int acc = 0;               // forward: 1 where the t-first rows fold z (shorter chains of roundings)
   int fmode = 1;             // forward: 2 when every position of every unit has its rows (no masks)
   int parts = 1, ncy = 1, kyt = 1, fused_mrow = 0;
   size_t fused_lds_bytes = 0, ifused_lds_bytes = 0;  // fwd 2; inv 2
@@ -113,7 +114,9 @@ struct Images {
   size_t y_fwd = 0, x_fwd = 0, y_inv = 0, x_inv = 0;  // axis images
   size_t z_blk = 0, t_blk = 0;                         // fused inverse + block epilogue
   // z-first rows: forward z basis, mode phases and t bases; inverse z basis,
-  // mode phases and t bases (only where ZRowCfg::fwd or inv)
+  // mode phases and t bases; phases of the columns of K_z K_t (only where
+  // ZRowCfg::fwd or inv, or blk == 2)
+  size_t zr_phase_col = 0;
   size_t zr_z_fwd = 0, zr_phase = 0, zr_t_fwd = 0, zr_t_fwd_adjoint_of_inverse = 0;
   size_t zr_z_inv = 0, zr_phase_inv = 0, zr_t_inv = 0, zr_t_inv_adjoint_of_forward = 0;
   size_t y_blk = 0;  // y expansion of dtst_inverse_block (y_inv unless the plan fuses y)

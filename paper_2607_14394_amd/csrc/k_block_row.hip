@@ -50,7 +50,7 @@ struct RowBlockArgs {
 template <int TH, int FOLD, int CI>
 __global__ void __launch_bounds__(64 * kRowWaves)
 inv_row_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, const float* __restrict__ wb,
-                     float* __restrict__ y, const float2* __restrict__ zimg, const float2* __restrict__ phase,
+                     float* __restrict__ y, const float2* __restrict__ zimg, const float4* __restrict__ phase,
                      const float* __restrict__ timg, ZRowArgs a, RowBlockArgs ba) {
   constexpr int NP = 1 + FOLD;  // z row sets
   extern __shared__ float4 lds[];
@@ -104,7 +104,7 @@ inv_row_block_kernel(const float2* __restrict__ in, const float* __restrict__ x,
       float2 nxt[1][4][2];
       load(it + kRowWaves < n_items ? it + kRowWaves : it, nxt);
       const int n = it % ba.nt16;
-      const float2 ph = phase[n * 64 + lane];
+      const float4 ph = phase[n * 64 + lane];
       v4f A[TH], B[TH];
 #pragma unroll
       for (int h = 0; h < TH; ++h) {
@@ -118,9 +118,8 @@ inv_row_block_kernel(const float2* __restrict__ in, const float* __restrict__ x,
         (void)zinv_index(a, m, g, n, kg, 0, &okp);
         (void)zinv_index(a, m, g, n, kg, 1, &okn);
         const float2 p = okp ? cur[0][kg][0] : make_float2(0.f, 0.f), q = okn ? cur[0][kg][1] : make_float2(0.f, 0.f);
-        const float pr = p.x * ph.x + p.y * ph.y, pi = p.y * ph.x - p.x * ph.y;
-        const float qr = q.x * ph.x - q.y * ph.y, qi = q.y * ph.x + q.x * ph.y;
-        const float a0 = pr + qr, a1 = -(pi + qi), b0 = qi - pi, b1 = qr - pr;
+        float a0, a1, b0, b1;
+        zinv_ab<FOLD, 0>(p, q, ph, &a0, &a1, &b0, &b1);
 #pragma unroll
         for (int h = 0; h < TH; ++h) {
           const float t0 = tl[((h * ba.kg + kg) * 2 + 0) * 64 + lane], t1 = tl[((h * ba.kg + kg) * 2 + 1) * 64 + lane];
@@ -296,7 +295,7 @@ int launch_inv_row_block(const ZRowCfg& c, const StreamCfg& s, int grid_resident
   const int grid = static_cast<int>(groups < grid_resident ? groups : grid_resident);
   const float2* in2 = static_cast<const float2*>(in);
   const float2* z = reinterpret_cast<const float2*>(zimg);
-  const float2* p = reinterpret_cast<const float2*>(phase);
+  const float4* p = reinterpret_cast<const float4*>(phase);
   void* args[] = {&in2, &x, &w, &y, &z, &p, &timg, &a, &ba};
   return hipLaunchKernel(pick(c, ci), dim3(grid), dim3(64 * kRowWaves), args, lds_of(c, ci, co),
                          static_cast<hipStream_t>(stream));

@@ -19,7 +19,9 @@
 // step, 4 TH contiguous bytes; 16 lanes a whole row), N = mode k, K =
 // position.  The accumulators are, register for register, the B operand of
 // the t contraction (M = k_t, N = k, K = t), and the combination of P, Q and f
-// stays in the lane (zfinish in zrow_ops.h).
+// stays in the lane (zfinish in zrow_ops.h).  The kernels that contract or expand y
+// as well apply f to the columns of the plane's spectrum instead, after (forward)
+// or before (inverse) y: fewer values than the rows'.
 //
 // Inverse.  With V = conj(f) Y[k], f Y[-k] and U = V C_t, the row is
 //   y(z) = sum_k cos(k z') (Re U+ + Re U-) + sin(k z') (Im U- - Im U+),
@@ -40,15 +42,18 @@ namespace {
 #include "zrow_ops.h"
 
 // TH: t groups; NT: 16-mode tiles of k = 0 .. kmax; MK: 1 when K_t <= 8 (Br
-// and Bi rows in one tile), else 2.
+// and Bi rows in one tile), else 2; ACC: shorter chains (zrow_ops.h).
 //
+// (ACC with two t groups: three waves per SIMD, its accumulators would spill at
+// four: 5 channels of 34 x 239 x 126 x 21 323 us at four, 193 at three, 258 without
+// ACC.)
 // Every wave walks its (row, unit) pairs with NB unit buffers, loads are
 // unconditional and past the last unit re-read the last row, as in
 // fwd_tz_body: the waits for one unit then cover that unit's loads only.
-template <int TH, int NT, int MK, int FOLD, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 ? 4 : 3)))
+template <int TH, int NT, int MK, int FOLD, int MODE, int ACC>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 && !(ACC && TH == 2) ? 4 : 3)))
 fwd_zrow_kernel(const float* __restrict__ x, float2* __restrict__ out, const float4* __restrict__ zimg,
-                const float2* __restrict__ phase, const float* __restrict__ timg, ZRowArgs a) {
+                const float4* __restrict__ phase, const float* __restrict__ timg, ZRowArgs a) {
   constexpr int NB = kZBufs;
   extern __shared__ float4 zl4[];
   const int nimg = a.units * NT * 2 * 64;
@@ -65,7 +70,7 @@ fwd_zrow_kernel(const float* __restrict__ x, float2* __restrict__ out, const flo
   for (int s = 0; s < TH * 4; ++s)
 #pragma unroll
     for (int k = 0; k < MK; ++k) ta[s][k] = timg[(s * MK + k) * 64 + lane];
-  float2 ph[NT];
+  float4 ph[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) ph[n] = phase[n * 64 + lane];
   __syncthreads();
@@ -95,7 +100,8 @@ fwd_zrow_kernel(const float* __restrict__ x, float2* __restrict__ out, const flo
 #pragma unroll
   for (int k = 0; k < NB; ++k) fetch(k);
 
-  v4f R[NT][TH], I[NT][TH];
+  constexpr int ZS = ACC && TH == 1 ? 2 : 1;
+  v4f R[ZS][NT][TH], I[ZS][NT][TH];
   auto step = [&](auto kc) __attribute__((always_inline)) {
     constexpr int k = decltype(kc)::value;
     const bool live = itp[k] < n_iter;
@@ -105,7 +111,7 @@ fwd_zrow_kernel(const float* __restrict__ x, float2* __restrict__ out, const flo
     fetch(k);
     if (!live || u != a.units - 1) return;
     float2* orow = out + r * int64_t(2 * a.kmax) * a.kt;
-    zfinish<TH, NT, MK>(R, I, ph, ta, a, l, [&](int e, v4f_c v, bool both) {
+    zfinish<TH, NT, MK, FOLD, ACC>(R, I, ph, ta, a, l, [&](int e, v4f_c v, bool both) {
       if (both) *reinterpret_cast<v4f_c*>(orow + e) = v;
       else orow[e] = make_float2(v[0], v[1]);
     });
@@ -123,7 +129,7 @@ fwd_zrow_kernel(const float* __restrict__ x, float2* __restrict__ out, const flo
 template <int TH, int NS, int KG, int FOLD, int T32>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NS <= 4 ? 4 : 3)))
 inv_zrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const float2* __restrict__ zimg,
-                const float2* __restrict__ phase, const float* __restrict__ timg, ZRowArgs a) {
+                const float4* __restrict__ phase, const float* __restrict__ timg, ZRowArgs a) {
   constexpr int NT = (NS + 3) / 4;
   extern __shared__ float2 zl2[];
   const int nimg = a.units * NS * 64;
@@ -144,7 +150,7 @@ inv_zrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const floa
     for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
       for (int e = 0; e < 2; ++e) tb[h][kg][e] = timg[((h * KG + kg) * 2 + e) * 64 + lane];
-  float2 ph[NT];
+  float4 ph[NT];
 #pragma unroll
   for (int n = 0; n < NT; ++n) ph[n] = phase[n * 64 + lane];
   __syncthreads();
@@ -156,7 +162,7 @@ inv_zrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const floa
   zinv_load<NT, KG>(in + wave * spec_len, a, m, g, un);
   for (int64_t r = wave; r < a.rows; r += wstride) {
     v4f A[NT][TH], B[NT][TH];
-    zinv_t<TH, NT, KG>(un, ph, tb, a, m, g, A, B);
+    zinv_t<TH, NT, KG, FOLD>(un, ph, tb, a, m, g, A, B);
     zinv_load<NT, KG>(in + (r + wstride < a.rows ? r + wstride : r) * spec_len, a, m, g, un);
     zinv_z<TH, NS, FOLD, T32>(A, B, zl2, a, m, g, y + r * row_len);
   }
@@ -167,10 +173,14 @@ const void* kernel_of(F* f) {
   return reinterpret_cast<const void*>(f);
 }
 
+template <int TH, int NT, int MK, int ACC>
+const void* pick_f4(const ZRowCfg& c) {
+  return c.fmode == 2 ? kernel_of(fwd_zrow_kernel<TH, NT, MK, 1, 2, ACC>) : kernel_of(fwd_zrow_kernel<TH, NT, MK, 1, 1, ACC>);
+}
 template <int TH, int NT, int MK>
 const void* pick_f3(const ZRowCfg& c) {
-  if (c.fold) return c.fmode == 2 ? kernel_of(fwd_zrow_kernel<TH, NT, MK, 1, 2>) : kernel_of(fwd_zrow_kernel<TH, NT, MK, 1, 1>);
-  return kernel_of(fwd_zrow_kernel<TH, NT, MK, 0, 1>);
+  if (!c.fold) return kernel_of(fwd_zrow_kernel<TH, NT, MK, 0, 1, 0>);
+  return c.acc ? pick_f4<TH, NT, MK, 1>(c) : pick_f4<TH, NT, MK, 0>(c);
 }
 template <int TH>
 const void* pick_f2(const ZRowCfg& c) {
@@ -248,7 +258,7 @@ int launch_fwd_zrow(const ZRowCfg& c, const StreamCfg& s, const float* x, void* 
   ZRowArgs a = args_of(c, s, rows);
   float2* o = static_cast<float2*>(out);
   const float4* z = reinterpret_cast<const float4*>(zimg);
-  const float2* p = reinterpret_cast<const float2*>(phase);
+  const float4* p = reinterpret_cast<const float4*>(phase);
   void* args[] = {&x, &o, &z, &p, &timg, &a};
   return hipLaunchKernel(pick_f(c), dim3(grid_for(c.grid_fwd, rows)), dim3(256), args, lds_fwd(c),
                          static_cast<hipStream_t>(stream));
@@ -260,7 +270,7 @@ int launch_inv_zrow(const ZRowCfg& c, const StreamCfg& s, const void* in, float*
   ZRowArgs a = args_of(c, s, rows);
   const float2* i = static_cast<const float2*>(in);
   const float2* z = reinterpret_cast<const float2*>(zimg);
-  const float2* p = reinterpret_cast<const float2*>(phase);
+  const float4* p = reinterpret_cast<const float4*>(phase);
   void* args[] = {&i, &y, &z, &p, &timg, &a};
   return hipLaunchKernel(pick_i(c, s.nt), dim3(grid_for(c.grid_inv, rows)), dim3(256), args, lds_inv(c),
                          static_cast<hipStream_t>(stream));

@@ -31,11 +31,14 @@ namespace {
 
 constexpr int kYWaves = 8;
 
-// MODE 2: N_z a multiple of 32, whole units without masks.
-template <int TH, int NT, int MK, int FOLD, int MODE, int NCY, int KYT>
-__global__ void __launch_bounds__(64 * kYWaves)
+// MODE 2: N_z a multiple of 32, whole units without masks.  ACC: shorter chains
+// of roundings (zrow_ops.h).  Two workgroups a CU where 128 registers hold the
+// accumulators (one t group, one y tile): 28 channels of 21 x 21 x 28 x 8 19.3 us
+// without ACC, 23.2 with it and 131 registers, 20.8 with it and 128.
+template <int TH, int NT, int MK, int FOLD, int MODE, int NCY, int KYT, int ACC>
+__global__ void __launch_bounds__(64 * kYWaves) __attribute__((amdgpu_waves_per_eu(TH == 1 && NCY == 1 && KYT == 1 ? 4 : 2)))
 fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const float4* __restrict__ zimg,
-               const float2* __restrict__ phase, const float* __restrict__ timg, const float4* __restrict__ yimg,
+               const float4* __restrict__ phase, const float* __restrict__ timg, const float4* __restrict__ yimg,
                ZRowArgs a, ZPlaneArgs f) {
   constexpr int NB = kZBufs, NW = kYWaves;
   constexpr int SPW = 16 / NW;         // slots of a group per wave
@@ -57,9 +60,9 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
   for (int s = 0; s < TH * 4; ++s)
 #pragma unroll
     for (int k = 0; k < MK; ++k) ta[s][k] = timg[(s * MK + k) * 64 + lane];
-  float2 ph[NT];
+  float4 ph[MTW];  // half-position phases of this lane's columns
 #pragma unroll
-  for (int n = 0; n < NT; ++n) ph[n] = phase[n * 64 + lane];
+  for (int t = 0; t < MTW; ++t) ph[t] = FOLD ? phase[min(16 * (w + NW * t) + (lane & 15), f.mcols - 1)] : float4{};
 
   const ZLane l = zlane<TH>(a);
   const int m = l.m, g = l.g;
@@ -122,7 +125,8 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
         yr[c][k][t] = v4f{0.f, 0.f, 0.f, 0.f};
         yi[c][k][t] = v4f{0.f, 0.f, 0.f, 0.f};
       }
-  v4f R[NT][TH], I[NT][TH];
+  constexpr int ZS = 1 + ACC;
+  v4f R[ZS][NT][TH], I[ZS][NT][TH];
 
   // As fwd_tzy_kernel's process: contract buffer k's unit, refill the buffer,
   // at a row's end leave its results in LDS, and after the wave's last row of
@@ -139,7 +143,7 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
     zload<TH, FOLD, MODE>(x + row_of(far, &vb[k]) * row_len, a, l, far.u, xb[k]);
     if (!live || c.u != a.units - 1) return;
     float2* vrow = vlds + (c.h * 16 + w + NW * c.j) * f.mrow;
-    zfinish<TH, NT, MK>(R, I, ph, ta, a, l, [&](int e, v4f_c v, bool both) {
+    zfinish<TH, NT, MK, 0, ACC>(R, I, {}, ta, a, l, [&](int e, v4f_c v, bool both) {
       vrow[e] = valid ? make_float2(v[0], v[1]) : make_float2(0.f, 0.f);
       if (both) vrow[e + 1] = valid ? make_float2(v[2], v[3]) : make_float2(0.f, 0.f);
     });
@@ -167,6 +171,15 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
 #pragma unroll
         for (int i = 0; i < 4; ++i) vs[c2][i] = vlds[(16 * c2 + 4 * g + i) * f.mrow + mc];
       __builtin_amdgcn_sched_barrier(0);
+      // ACC: the products of Im of the basis in a chain of their own per group
+      v4f pr[NCY][KYT], pi[NCY][KYT];
+#pragma unroll
+      for (int cl = 0; cl < NCY; ++cl)
+#pragma unroll
+        for (int kk = 0; kk < KYT; ++kk) {
+          pr[cl][kk] = ACC ? v4f{0.f, 0.f, 0.f, 0.f} : yr[cl][kk][t];
+          pi[cl][kk] = ACC ? v4f{0.f, 0.f, 0.f, 0.f} : yi[cl][kk][t];
+        }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float2 va = vs[0][i];
@@ -182,12 +195,21 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
         for (int cl = 0; cl < NCY; ++cl)
 #pragma unroll
           for (int kk = 0; kk < KYT; ++kk) {
-            yr[cl][kk][t] = mfma(br[cl][kk][i], xs[cl].x, yr[cl][kk][t]);
-            yi[cl][kk][t] = mfma(br[cl][kk][i], xs[cl].y, yi[cl][kk][t]);
-            yr[cl][kk][t] = mfma(bi[cl][kk][i], -xs[cl].y, yr[cl][kk][t]);
-            yi[cl][kk][t] = mfma(bi[cl][kk][i], xs[cl].x, yi[cl][kk][t]);
+            v4f& r = ACC ? yr[cl][kk][t] : pr[cl][kk];
+            v4f& q = ACC ? yi[cl][kk][t] : pi[cl][kk];
+            r = mfma(br[cl][kk][i], xs[cl].x, r);
+            q = mfma(br[cl][kk][i], xs[cl].y, q);
+            pr[cl][kk] = mfma(bi[cl][kk][i], -xs[cl].y, pr[cl][kk]);
+            pi[cl][kk] = mfma(bi[cl][kk][i], xs[cl].x, pi[cl][kk]);
           }
       }
+#pragma unroll
+      for (int cl = 0; cl < NCY; ++cl)
+#pragma unroll
+        for (int kk = 0; kk < KYT; ++kk) {
+          yr[cl][kk][t] = ACC ? yr[cl][kk][t] + pr[cl][kk] : pr[cl][kk];
+          yi[cl][kk][t] = ACC ? yi[cl][kk][t] + pi[cl][kk] : pi[cl][kk];
+        }
       if (c.q == c.q1 - 1) {
         // part done: rows p of K_y (class cl, slot 16kk + 4g + i), columns mc
         float2* op = out + c.it * int64_t(f.ky) * f.mcols;
@@ -199,8 +221,8 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
             for (int i = 0; i < 4; ++i) {
               const int sl = 16 * kk + 4 * g + i;
               const int p = NCY == 2 ? 2 * sl + cl : sl;
-              if (p < f.ky && mc < f.mcols)
-                op[int64_t(p) * f.mcols + mc] = make_float2(yr[cl][kk][t][i], yi[cl][kk][t][i]);
+              const float2 v = make_float2(yr[cl][kk][t][i], yi[cl][kk][t][i]);
+              if (p < f.ky && mc < f.mcols) op[int64_t(p) * f.mcols + mc] = FOLD ? turn<1>(v.x, v.y, ph[t]) : v;
             }
             yr[cl][kk][t] = v4f{0.f, 0.f, 0.f, 0.f};
             yi[cl][kk][t] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -218,16 +240,17 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
   } while (cb[0].it < f.items);
 }
 
-template <int TH, int NT, int MK, int FOLD, int MODE>
-const void* pick_y(int ncy, int kyt) {
-  if (ncy == 2) return reinterpret_cast<const void*>(fwd_zty_kernel<TH, NT, MK, FOLD, MODE, 2, 1>);
-  return reinterpret_cast<const void*>(kyt == 1 ? fwd_zty_kernel<TH, NT, MK, FOLD, MODE, 1, 1>
-                                                : fwd_zty_kernel<TH, NT, MK, FOLD, MODE, 1, 2>);
+template <int TH, int NT, int MK, int FOLD, int MODE, int ACC>
+const void* pick_y(const ZRowCfg& c) {
+  if (c.ncy == 2) return reinterpret_cast<const void*>(fwd_zty_kernel<TH, NT, MK, FOLD, MODE, 2, 1, ACC>);
+  return reinterpret_cast<const void*>(c.kyt == 1 ? fwd_zty_kernel<TH, NT, MK, FOLD, MODE, 1, 1, ACC>
+                                                  : fwd_zty_kernel<TH, NT, MK, FOLD, MODE, 1, 2, ACC>);
 }
 template <int TH, int NT, int MK>
 const void* pick_fold(const ZRowCfg& c) {
-  if (!c.fold) return pick_y<TH, NT, MK, 0, 1>(c.ncy, c.kyt);
-  return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2>(c.ncy, c.kyt) : pick_y<TH, NT, MK, 1, 1>(c.ncy, c.kyt);
+  if (!c.fold) return pick_y<TH, NT, MK, 0, 1, 0>(c);
+  if (c.acc) return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2, 1>(c) : pick_y<TH, NT, MK, 1, 1, 1>(c);
+  return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2, 0>(c) : pick_y<TH, NT, MK, 1, 1, 0>(c);
 }
 // The combinations that plans take (zty_covers in tables.cpp): two t groups
 // with one mode tile, one t group with K_t <= 8.
@@ -283,7 +306,7 @@ int launch_fwd_zty(const ZRowCfg& c, const StreamCfg& s, const AxisCfg& ay, cons
   const int grid = f.items < c.grid_fused ? f.items : c.grid_fused;
   float2* o = static_cast<float2*>(out);
   const float4* z = reinterpret_cast<const float4*>(zimg);
-  const float2* p = reinterpret_cast<const float2*>(phase);
+  const float4* p = reinterpret_cast<const float4*>(phase);
   const float4* yi = reinterpret_cast<const float4*>(yimg);
   void* args[] = {&x, &o, &z, &p, &timg, &yi, &a, &f};
   return hipLaunchKernel(pick(c), dim3(grid), dim3(64 * kYWaves), args, c.fused_lds_bytes,

@@ -25,7 +25,7 @@ namespace {
 template <int TH, int NS, int KG, int T32, int NCY, int JQY>
 __global__ void __launch_bounds__(1024)
 inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const float2* __restrict__ zimg,
-                 const float2* __restrict__ phase, const float* __restrict__ timg, const float4* __restrict__ yimg,
+                 const float4* __restrict__ phase, const float* __restrict__ timg, const float4* __restrict__ yimg,
                  ZRowArgs a, ZPlaneArgs f) {
   constexpr int NT = (NS + 3) / 4;
   // LDS: the y image, the z image, the exchanged rows
@@ -47,6 +47,7 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
   const int mc = 16 * w + m;
   const bool col_ok = mc < f.mcols;
   float2 u[NCY][JQY][4];
+  const float4 ph = phase[min(mc, f.mcols - 1)];  // the column's half-position phase
   {
     const float2* sp = in + pl * int64_t(f.ky) * f.mcols;
 #pragma unroll
@@ -69,21 +70,26 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
     for (int kg = 0; kg < KG; ++kg)
 #pragma unroll
       for (int e = 0; e < 2; ++e) tb[h][kg][e] = timg[((h * KG + kg) * 2 + e) * 64 + lane];
-  float2 ph[NT];
-#pragma unroll
-  for (int n = 0; n < NT; ++n) ph[n] = phase[n * 64 + lane];
   for (int i = threadIdx.x; i < f.yimg_n4; i += blockDim.x) lds[i] = yimg[i];
   for (int i = threadIdx.x; i < nimg; i += blockDim.x) zl2[i] = zimg[i];
   __syncthreads();
 
+  // (after the staging, so that the spectrum's loads stay in flight across it)
+#pragma unroll
+  for (int cl = 0; cl < NCY; ++cl)
+#pragma unroll
+    for (int q = 0; q < JQY; ++q)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u[cl][q][i] = turn<1>(u[cl][q][i].x, u[cl][q][i].y, conj_phase(ph));
+
   const int64_t row_len = int64_t(a.nz) * (T32 ? 32 : a.nt);
   for (int gq = q0; gq < q1; ++gq) {
     if (16 * w < f.mcols) {
-      v4f er[NCY], ei[NCY];
+      v4f er[NCY], ei[NCY], fr[NCY], fi[NCY];  // products of Re and of Im of the basis (a chain of roundings each)
 #pragma unroll
       for (int cl = 0; cl < NCY; ++cl) {
         er[cl] = v4f{0.f, 0.f, 0.f, 0.f};
-        ei[cl] = v4f{0.f, 0.f, 0.f, 0.f};
+        ei[cl] = fr[cl] = fi[cl] = er[cl];
       }
 #pragma unroll
       for (int q = 0; q < JQY; ++q)
@@ -97,10 +103,15 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
             const float2 v = u[cl][q][i];
             er[cl] = mfma(br[i], v.x, er[cl]);
             ei[cl] = mfma(br[i], v.y, ei[cl]);
-            er[cl] = mfma(bi[i], -v.y, er[cl]);
-            ei[cl] = mfma(bi[i], v.x, ei[cl]);
+            fr[cl] = mfma(bi[i], -v.y, fr[cl]);
+            fi[cl] = mfma(bi[i], v.x, fi[cl]);
           }
         }
+#pragma unroll
+      for (int cl = 0; cl < NCY; ++cl) {
+        er[cl] += fr[cl];
+        ei[cl] += fi[cl];
+      }
       // accumulator register i holds slot 4g + i, column mc
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -121,7 +132,7 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
         float2 un[NT][KG][2];
         zinv_load<NT, KG>(vlds + (h * 16 + w) * f.mrow, a, m, g, un);
         v4f A[NT][TH], B[NT][TH];
-        zinv_t<TH, NT, KG>(un, ph, tb, a, m, g, A, B);
+        zinv_t<TH, NT, KG, 0>(un, {}, tb, a, m, g, A, B);
         zinv_z<TH, NS, 1, T32>(A, B, zl2, a, m, g, y + (int64_t(pl) * f.ny + s + h * f.half) * row_len);
       }
     }
@@ -203,7 +214,7 @@ int launch_inv_yzrow(const ZRowCfg& c, const StreamCfg& s, const AxisCfg& ay, co
   f.mrow = c.fused_mrow;
   f.yimg_n4 = ay.ktiles * ay.JQ * (ay.fold == 2 ? 2 : 1) * 2 * 64;
   const float2* z = reinterpret_cast<const float2*>(zimg);
-  const float2* p = reinterpret_cast<const float2*>(phase);
+  const float4* p = reinterpret_cast<const float4*>(phase);
   const float4* yi = reinterpret_cast<const float4*>(yimg);
   for (int64_t p0 = 0; p0 < planes; p0 += kInvPlanesPerLaunch) {
     const int64_t n = std::min(planes - p0, kInvPlanesPerLaunch);

@@ -102,6 +102,7 @@ bool z_first(const StreamCfg& s, bool whole_z, ZRowCfg* out) {
   z.steps = static_cast<int>(ceil_div(z.np, 4));
   z.units = static_cast<int>(ceil_div(z.np, 16));
   z.fmode = z.fold && s.nz % 32 == 0 ? 2 : 1;
+  z.acc = s.ncls > 1 ? 1 : 0;
   // z bases in LDS, four workgroups a CU
   if (z.units * size_t(z.ntl) * 2 * 64 * 16 > 40 * 1024 || z.units * size_t(z.ns) * 64 * 8 > 40 * 1024) return false;
   *out = z;
@@ -508,11 +509,12 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   if (dv.zr.fwd || dv.zr.inv || dv.blk == 2) {
     const ZRowCfg& z = dv.zr;
     im.zr_z_fwd = take(size_t(z.units) * z.ntl * 2 * 64 * 4);
-    im.zr_phase = take(size_t(z.ntl) * 64 * 2);
+    im.zr_phase = take(size_t(z.ntl) * 64 * 4);
     im.zr_t_fwd = take(size_t(z.th) * 4 * z.mk * 64);
     im.zr_t_fwd_adjoint_of_inverse = take(size_t(z.th) * 4 * z.mk * 64);
     im.zr_z_inv = take(size_t(z.units) * z.ns * 64 * 2);
-    im.zr_phase_inv = take(ceil_div(z.ns, 4) * 64 * 2);
+    im.zr_phase_inv = take(ceil_div(z.ns, 4) * 64 * 4);
+    im.zr_phase_col = take(size_t(nn_y) * 4);
     im.zr_t_inv = take(size_t(z.th) * 4 * z.mk * 64);
     im.zr_t_inv_adjoint_of_forward = take(size_t(z.th) * 4 * z.mk * 64);
   }
@@ -704,8 +706,10 @@ void z_inverse_image(const Derived& dv, float* dst) {
 // where z folds (2 pi k (2z + 1) / 2N_z), else at the global z.
 //   forward z: float4 entry ((u*NT + n)*2 + part)*64 + lane, component st: Re
 //     (part 0) or Im of exp(-i angle) of mode k = 16n + m at position 16u + 4st + g;
-//   phases: float2 entry n*64 + lane: exp(i pi k / N_z) of k = 16n + m (forward)
-//     or k = 16n + 4(m & 3) + (m >> 2) (inverse) where z folds, else 1;
+//   phases: float4 entry n*64 + lane: exp(i pi k / N_z) of k = 16n + m (forward)
+//     or k = 16n + 4(m & 3) + (m >> 2) (inverse) where z folds, else 1; real and
+//     imaginary part, then what rounding them to 32 bits left out;
+//   column phases: the same for each column of K_z K_t (k of its z mode, signed);
 //   forward t: entry ((4j + i)*MK + kk)*64 + lane: K index g of step (j, i) is
 //     t = TH (4g + i) + j (lanes past the extent hold its last TH values
 //     again, with zeros), rows M = 4g' + i': with MK = 2 tile kk is part kk of B_t at
@@ -736,11 +740,19 @@ void zrow_images(const Derived& dv, float* base) {
     if (z.fold) twiddle(2 * N, k, 1, &re, &im_);  // exp(-i pi k / N)
     base[at] = static_cast<float>(re);
     base[at + 1] = static_cast<float>(-im_);
+    base[at + 2] = static_cast<float>(re - base[at]);
+    base[at + 3] = static_cast<float>(-im_ - base[at + 1]);
   };
+  for (int c = 0; c < sc.kz * sc.kt; ++c) {
+    const int p = c / sc.kt, k = p < kmax ? p : 2 * kmax - p;  // |k| of the column
+    float* e = base + im.zr_phase_col + size_t(c) * 4;
+    put_phase(im.zr_phase_col + size_t(c) * 4, k);
+    if (p >= kmax) e[1] = -e[1], e[3] = -e[3];
+  }
   for (int lane = 0; lane < 64; ++lane) {
     const int m = lane & 15, g = lane >> 4;
     for (int n = 0; n < z.ntl; ++n) {
-      put_phase(im.zr_phase + size_t(n * 64 + lane) * 2, 16 * n + m);
+      put_phase(im.zr_phase + size_t(n * 64 + lane) * 4, 16 * n + m);
       for (int u = 0; u < z.units; ++u)
         for (int st = 0; st < 4; ++st) {
           zval(16 * n + m, 16 * u + 4 * st + g);
@@ -750,7 +762,7 @@ void zrow_images(const Derived& dv, float* base) {
         }
     }
     for (int n = 0; n < ceil_div(z.ns, 4); ++n)
-      put_phase(im.zr_phase_inv + size_t(n * 64 + lane) * 2, 16 * n + 4 * (m & 3) + (m >> 2));
+      put_phase(im.zr_phase_inv + size_t(n * 64 + lane) * 4, 16 * n + 4 * (m & 3) + (m >> 2));
     for (int zt = 0; zt < z.units; ++zt)
       for (int s = 0; s < z.ns; ++s) {
         zval(4 * s + g, 16 * zt + m);

@@ -86,21 +86,32 @@ __device__ __forceinline__ void zload(const float* xr, const ZRowArgs& a, const 
   }
 }
 
+// ACC: shorter chains of roundings, for rows whose t-first form folds z into
+// classes and so has short chains too (ZRowCfg::acc).  The K steps of the z
+// products then go to ZS = 2 accumulator sets in turn where the registers allow
+// it, the t products of a row form two chains, and the phases are applied with
+// what rounding them left out; the fused kernels keep the products of Re and Im
+// of the y basis in chains of their own.  Forward of 16 x 24 x 144 x 12, modes
+// 8/9/12/5, error against 64 bits: 2.16e-7 without, 1.79e-7 with (t first 1.86e-7);
+// 64^3 x 16, 16 channels: 68.3 us without, 71.6 with (t first 76).
+
 // Contracts one unit into the row's accumulators: R with the cosines of the
 // sums, I with the (negative) sines of the differences.  zl4: float4 (four
 // steps) of the unit's cosine and sine tiles.  MODE 2: every position and
 // partner exists.
-template <int TH, int NT, int FOLD, int MODE>
+template <int TH, int NT, int FOLD, int MODE, int ZS>
 __device__ __forceinline__ void zunit(const float (&xv)[4][1 + FOLD][TH], const float4* zl4, const ZRowArgs& a,
-                                      const ZLane& l, int u, v4f (&R)[NT][TH], v4f (&I)[NT][TH]) {
+                                      const ZLane& l, int u, v4f (&R)[ZS][NT][TH], v4f (&I)[ZS][NT][TH]) {
   if (u == 0) {
 #pragma unroll
-    for (int n = 0; n < NT; ++n)
+    for (int p = 0; p < ZS; ++p)
 #pragma unroll
-      for (int j = 0; j < TH; ++j) {
-        R[n][j] = v4f{0.f, 0.f, 0.f, 0.f};
-        I[n][j] = v4f{0.f, 0.f, 0.f, 0.f};
-      }
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int j = 0; j < TH; ++j) {
+          R[p][n][j] = v4f{0.f, 0.f, 0.f, 0.f};
+          I[p][n][j] = v4f{0.f, 0.f, 0.f, 0.f};
+        }
   }
   float4 c[NT], s[NT];
 #pragma unroll
@@ -130,40 +141,60 @@ __device__ __forceinline__ void zunit(const float (&xv)[4][1 + FOLD][TH], const 
     for (int n = 0; n < NT; ++n)
 #pragma unroll
       for (int j = 0; j < TH; ++j) {
-        R[n][j] = mfma(f[j], at(c[n]), R[n][j]);
-        I[n][j] = mfma(d[j], at(s[n]), I[n][j]);
+        v4f& r = R[st % ZS][n][j];
+        v4f& i = I[st % ZS][n][j];
+        r = mfma(f[j], at(c[n]), r);
+        i = mfma(d[j], at(s[n]), i);
       }
   }
 }
 
+// (x + i y) (c + i s) of a phase c + i s = (ph.x + ph.z) + i (ph.y + ph.w), the
+// second parts what rounding the first left out (ACC = 0: without them).
+template <int ACC>
+__device__ __forceinline__ float2 turn(float x, float y, const float4& ph) {
+  if constexpr (!ACC) return make_float2(fmaf(x, ph.x, -(y * ph.y)), fmaf(y, ph.x, x * ph.y));
+  return make_float2(fmaf(x, ph.x, fmaf(-y, ph.y, fmaf(x, ph.z, -(y * ph.w)))),
+                     fmaf(y, ph.x, fmaf(x, ph.y, fmaf(y, ph.z, x * ph.w))));
+}
+__device__ __forceinline__ float4 conj_phase(const float4& ph) { return make_float4(ph.x, -ph.y, ph.z, -ph.w); }
+
 // Finishes a row.  Lane (m, g) holds mode k = 16n + m, t = TH (4g + i) + j in
-// register i of R[n][j] (Re) and I[n][j] (Im).  The t contraction of both
+// register i of R[.][n][j] (Re) and I[.][n][j] (Im).  The t contraction of both
 // gives P and Q (k_t rows, B_t = Br + i Bi), and the modes are
 //   X[k] = f (P + i Q),   X[-k] = conj(f) (P - i Q),
-// f the mode's half-position phase.  st(index, v) takes the coefficients of
-// k_t and k_t + 1 at index = p K_t + k_t; `both` false: of k_t only.
-template <int TH, int NT, int MK, class St>
-__device__ __forceinline__ void zfinish(const v4f (&R)[NT][TH], const v4f (&I)[NT][TH], const float2 (&ph)[NT],
-                                        const float (&ta)[TH * 4][MK], const ZRowArgs& a, const ZLane& l, St&& st) {
+// f the mode's half-position phase (PH = 0: left to the caller, who applies it
+// after the y contraction, to fewer values).  st(index, v) takes the coefficients
+// of k_t and k_t + 1 at index = p K_t + k_t; `both` false: of k_t only.
+template <int TH, int NT, int MK, int PH, int ACC, int ZS, class St>
+__device__ __forceinline__ void zfinish(const v4f (&R)[ZS][NT][TH], const v4f (&I)[ZS][NT][TH],
+                                        const float4 (&ph)[NT], const float (&ta)[TH * 4][MK], const ZRowArgs& a,
+                                        const ZLane& l, St&& st) {
+  constexpr int TC = ACC ? 2 : 1;  // chains
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
     v4f P[MK], Q[MK];
 #pragma unroll
-    for (int kk = 0; kk < MK; ++kk) {
-      P[kk] = v4f{0.f, 0.f, 0.f, 0.f};
-      Q[kk] = v4f{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int c = 0; c < TC; ++c)
 #pragma unroll
-    for (int j = 0; j < TH; ++j)
+      for (int kk = 0; kk < MK; ++kk) {
+        v4f p = v4f{0.f, 0.f, 0.f, 0.f}, q = p;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < TH; ++j)
 #pragma unroll
-        for (int kk = 0; kk < MK; ++kk) {
-          P[kk] = mfma(ta[4 * j + i][kk], R[n][j][i], P[kk]);
-          Q[kk] = mfma(ta[4 * j + i][kk], I[n][j][i], Q[kk]);
-        }
+          for (int i = 4 / TC * c; i < 4 / TC * (c + 1); ++i) {
+            float r = R[0][n][j][i], im = I[0][n][j][i];
+            if constexpr (ZS == 2) {
+              r += R[ZS - 1][n][j][i];
+              im += I[ZS - 1][n][j][i];
+            }
+            p = mfma(ta[4 * j + i][kk], r, p);
+            q = mfma(ta[4 * j + i][kk], im, q);
+          }
+        P[kk] = c == 0 ? p : P[kk] + p;
+        Q[kk] = c == 0 ? q : Q[kk] + q;
+      }
     const int k = 16 * n + l.m;
-    const float fr = ph[n].x, fi = ph[n].y;
 #pragma unroll
     for (int e = 0; e < MK; ++e) {
       // k_t = 8e + 2g + i: Br products in register 2e + i of tile 0 (MK = 1:
@@ -173,11 +204,16 @@ __device__ __forceinline__ void zfinish(const v4f (&R)[NT][TH], const v4f (&I)[N
       for (int i = 0; i < 2; ++i) {
         const int r0 = MK == 2 ? 2 * e + i : i, r1 = MK == 2 ? 2 * e + i : 2 + i;
         const float pr = P[0][r0], pi = P[MK - 1][r1], qr = Q[0][r0], qi = Q[MK - 1][r1];
-        const float ur = pr - qi, ui = pi + qr, dr = pr + qi, di = pi - qr;
-        up[2 * i] = ur * fr - ui * fi;
-        up[2 * i + 1] = ur * fi + ui * fr;
-        dn[2 * i] = dr * fr + di * fi;
-        dn[2 * i + 1] = di * fr - dr * fi;
+        float2 u = make_float2(pr - qi, pi + qr), d = make_float2(pr + qi, pi - qr);
+        if constexpr (PH) {
+          // (with two tiles of modes and two t groups the registers spill)
+          u = turn<ACC && NT * TH < 4>(u.x, u.y, ph[n]);
+          d = turn<ACC && NT * TH < 4>(d.x, d.y, conj_phase(ph[n]));
+        }
+        up[2 * i] = u.x;
+        up[2 * i + 1] = u.y;
+        dn[2 * i] = d.x;
+        dn[2 * i + 1] = d.y;
       }
       const int kt = 8 * e + 2 * l.g;
       if (kt < a.kt) {
@@ -218,36 +254,62 @@ __device__ __forceinline__ void zinv_load(const float2* u, const ZRowArgs& a, in
       }
 }
 
+// A operands of the t expansion from p = Y[k], q = Y[-k] (zero where not
+// retained) and the mode's phase f (PH = 0: p and q have it already): with
+// V+ = conj(f) p and V- = f q,
+//   a0 = Re V+ + Re V-,  a1 = -(Im V+ + Im V-),  b0 = Im V- - Im V+,  b1 = Re V- - Re V+.
+template <int PH, int ACC>
+__device__ __forceinline__ void zinv_ab(float2 p, float2 q, const float4& ph, float* a0, float* a1, float* b0,
+                                        float* b1) {
+  if constexpr (PH) {
+    p = turn<ACC>(p.x, p.y, conj_phase(ph));
+    q = turn<ACC>(q.x, q.y, ph);
+  }
+  *a0 = p.x + q.x;
+  *a1 = -(p.y + q.y);
+  *b0 = q.y - p.y;
+  *b1 = q.x - p.x;
+}
+
 // t expansion of a row: A (cosine) and B (sine) parts, tb the B operand
-// (column t, K index k_t = 4kg + g; Re and Im of C_t).
-template <int TH, int NT, int KG>
-__device__ __forceinline__ void zinv_t(const float2 (&un)[NT][KG][2], const float2 (&ph)[NT],
+// (column t, K index k_t = 4kg + g; Re and Im of C_t, with K_t <= 8 a chain of
+// roundings each: the t-first form of such rows may fold z into four classes).
+template <int TH, int NT, int KG, int PH>
+__device__ __forceinline__ void zinv_t(const float2 (&un)[NT][KG][2], const float4 (&ph)[NT],
                                        const float (&tb)[TH][KG][2], const ZRowArgs& a, int m, int g,
                                        v4f (&A)[NT][TH], v4f (&B)[NT][TH]) {
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
+    constexpr int ACC = KG == 2;
+    v4f A1[TH], B1[TH];
 #pragma unroll
     for (int h = 0; h < TH; ++h) {
       A[n][h] = v4f{0.f, 0.f, 0.f, 0.f};
-      B[n][h] = v4f{0.f, 0.f, 0.f, 0.f};
+      B[n][h] = A1[h] = B1[h] = A[n][h];
     }
-    const float fr = ph[n].x, fi = ph[n].y;
 #pragma unroll
     for (int kg = 0; kg < KG; ++kg) {
       bool okp, okn;
       (void)zinv_index(a, m, g, n, kg, 0, &okp);
       (void)zinv_index(a, m, g, n, kg, 1, &okn);
       const float2 p = okp ? un[n][kg][0] : make_float2(0.f, 0.f), q = okn ? un[n][kg][1] : make_float2(0.f, 0.f);
-      // V+ = conj(f) Y[k], V- = f Y[-k]
-      const float pr = p.x * fr + p.y * fi, pi = p.y * fr - p.x * fi;
-      const float qr = q.x * fr - q.y * fi, qi = q.y * fr + q.x * fi;
-      const float a0 = pr + qr, a1 = -(pi + qi), b0 = qi - pi, b1 = qr - pr;
+      float a0, a1, b0, b1;
+      zinv_ab<PH, ACC>(p, q, ph[n], &a0, &a1, &b0, &b1);
 #pragma unroll
       for (int h = 0; h < TH; ++h) {
         A[n][h] = mfma(a0, tb[h][kg][0], A[n][h]);
         B[n][h] = mfma(b0, tb[h][kg][0], B[n][h]);
-        A[n][h] = mfma(a1, tb[h][kg][1], A[n][h]);
-        B[n][h] = mfma(b1, tb[h][kg][1], B[n][h]);
+        v4f& aa = ACC ? A1[h] : A[n][h];
+        v4f& bb = ACC ? B1[h] : B[n][h];
+        aa = mfma(a1, tb[h][kg][1], aa);
+        bb = mfma(b1, tb[h][kg][1], bb);
+      }
+    }
+    if constexpr (ACC) {
+#pragma unroll
+      for (int h = 0; h < TH; ++h) {
+        A[n][h] += A1[h];
+        B[n][h] += B1[h];
       }
     }
   }
