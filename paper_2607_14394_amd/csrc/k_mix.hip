@@ -859,9 +859,23 @@ bool row_groups(int64_t ci, int64_t co, int64_t modes) {
   return co == 16 || (co == 32 && modes * ci * co * 8 < (int64_t(1) << 30));
 }
 
+// mix_h over several batch entries by row groups too where a lane holds one
+// column (an odd C_out): an element of w then costs two LDS accesses an entry,
+// which the row groups' register sums do not, unless most of their lanes idle
+// (65536 modes, B = 3: 13 -> 13 29.6 us and 42.9 by columns, 29 -> 29 121 and 170,
+// 21 -> 21 80 and 76).
+bool row_groups_h(int64_t B, int64_t ci, int64_t co) {
+  return co % 2 != 0 && B > 1 && (B * ci >= 32 || co > 32) && (co <= 7 || 10 * co >= 7 * lanes_per_row(co));
+}
+
 // Rows of w in flight: as many as C_in, or the count that leaves the fewest
-// unused ones.
-int rows_in_flight(int64_t ci) {
+// unused ones; but 8 where the registers of 16 or 20 cost more waves than their
+// loads hide: in mix for C_in of 13 to 20 (65536 modes of 20 -> 20: B = 1 38.1 and
+// 34.8 us, B = 3 62.9 and 43.4; by row groups 40.1 and 61.3), in mix_h over
+// several batch entries with two columns a lane, from 12 (B = 3: 80.1 and 55.7; at
+// B = 1 34.9 and 35.4).
+int rows_in_flight(int64_t ci, bool few) {
+  if (few) return 8;
   if (ci <= 20) return static_cast<int>((ci + 3) / 4 * 4);
   int best = 16;
   for (int r : {20, 12})
@@ -885,10 +899,12 @@ int launch_mix(const void* xhat, const void* w, void* yhat, int64_t B, int64_t c
                int64_t m0, int64_t m1, void* stream) {
   if (B <= 0 || m1 <= m0) return hipSuccess;
   if (co <= 64 && !row_groups(ci, co, m1 - m0)) {
-    const int cols = cols_of(co, w), r = rows_in_flight(ci);
+    const int cols = cols_of(co, w), r = rows_in_flight(ci, ci >= 13 && ci <= 20);
     const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, 0);
     const size_t lds = sizeof(float2) * size_t(B) * size_t(ci + co) * (a.mpb + 1);
-    if (lds <= 64 * 1024)
+    // (with up to four columns a block is up to 256 modes, whose input spectra then
+    // fill the LDS: 65536 modes of 20 -> 3, B = 3: 26.9 us, by row groups 16.9)
+    if (lds <= (co <= 4 && ci >= 12 ? 24 : 64) * 1024)
       return launch_pair(cols == 2 ? pick_mix_cols<2>(r) : pick_mix_cols<1>(r), lds, xhat, w, yhat, a, stream);
   }
   const MixArgs a = make_args(B, ci, co, M, m0, m1, 0);
@@ -902,8 +918,8 @@ int launch_mix_h(const void* gy, const void* w, void* gx, int64_t B, int64_t ci,
   // (a full wave per row, C_out = 64, sums it in registers faster: 32768 modes
   // of 12 -> 64, B = 3: 70 us below, 79 us through LDS; of 48 -> 48, B = 2: 165
   // below, 131 through LDS)
-  if (co < 64 && !row_groups(ci, co, m1 - m0)) {
-    const int cols = cols_of(co, w), r = rows_in_flight(ci);
+  if (co < 64 && !row_groups(ci, co, m1 - m0) && !row_groups_h(B, ci, co)) {
+    const int cols = cols_of(co, w), r = rows_in_flight(ci, B > 1 && ci >= 13 && co % 2 == 0 && co >= 12);
     const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, 0);
     const size_t lds = sizeof(float2) * (size_t(B) * size_t(ci + co) * (a.mpb + 1) + size_t(4) * r * 65);
     if (lds <= 80 * 1024)

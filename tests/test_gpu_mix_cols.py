@@ -12,7 +12,8 @@ from gpu_common import Guarded, check, desc_of, dev, geometry, np_of, rand_cplx,
 pytestmark = pytest.mark.gpu
 
 CASES = [(1, 1, 1), (2, 3, 2), (1, 5, 5), (1, 20, 20), (3, 4, 6), (2, 21, 9), (1, 33, 17), (1, 32, 32), (2, 7, 48),
-         (1, 13, 63), (2, 3, 64), (1, 2, 66)]
+         (1, 13, 63), (2, 3, 64), (1, 2, 66), (1, 13, 14), (2, 20, 12), (3, 17, 18), (3, 20, 3), (3, 13, 13),
+         (2, 17, 31), (3, 5, 7), (2, 4, 63)]
 
 
 @pytest.mark.parametrize("b,ci,co", CASES)
