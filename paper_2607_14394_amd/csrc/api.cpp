@@ -175,7 +175,8 @@ dtst_status run_forward_chain(const dtst_plan_st* p, int64_t channels, const flo
     w2 = w1;  // the planes' parts, no W1
     e = timed(K_FWD_TZY, stream, [&] {
       return dtst::launch_fwd_zty(dv.zr, dv.sc, dv.ay_f, x, w2, planes, static_cast<int>(dv.d.n_local[1]), zr_timg,
-                                  p->blob + im.zr_z_fwd, p->blob + im.zr_phase_col, p->blob + im.y_fwd, stream);
+                                  p->blob + im.zr_z_fwd, p->blob + (dv.zr.acc ? im.zr_phase_col : im.zr_phase),
+                                  p->blob + im.y_fwd, stream);
     });
     if (e != hipSuccess) return device_status(e, "z+t+y contraction launch");
   } else if (dv.sc.fuse_y && !dv.zr.fwd) {
@@ -224,7 +225,8 @@ dtst_status run_inverse_chain(const dtst_plan_st* p, int64_t channels, const voi
   if (dv.zr.inv == 2) {
     e = timed(K_INV_YZT, stream, [&] {
       return dtst::launch_inv_yzrow(dv.zr, dv.sc, dv.ay_i, v1, y, planes, static_cast<int>(dv.d.n_local[1]), zr_timg,
-                                    p->blob + im.zr_z_inv, p->blob + im.zr_phase_col, p->blob + im.y_inv, stream);
+                                    p->blob + im.zr_z_inv, p->blob + (dv.zr.mk == 1 ? im.zr_phase_col : im.zr_phase_inv),
+                                    p->blob + im.y_inv, stream);
     });
     return e == hipSuccess ? ok() : device_status(e, "y+t+z expansion launch");
   }

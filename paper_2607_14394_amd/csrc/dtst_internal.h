@@ -74,7 +74,7 @@ struct ZRowCfg {
   int th = 1, fold = 0, ntl = 1, ns = 0, mk = 1;  // (ns 0: rows the kernels do not cover)
   int np = 0, np2 = 0;
   int steps = 0, units = 0;  // ceil(np / 4), ceil(np / 16)
-  int acc = 0;               // forward: 1 where the t-first rows fold z (shorter chains of roundings)
+  int acc = 0;               // forward: shorter chains of roundings, 1 of y, 2 of the rows too (z_first)
   int fmode = 1;             // forward: 2 when every position of every unit has its rows (no masks)
   int parts = 1, ncy = 1, kyt = 1, fused_mrow = 0;
   size_t fused_lds_bytes = 0, ifused_lds_bytes = 0;  // fwd 2; inv 2

@@ -19,8 +19,8 @@
 // step, 4 TH contiguous bytes; 16 lanes a whole row), N = mode k, K =
 // position.  The accumulators are, register for register, the B operand of
 // the t contraction (M = k_t, N = k, K = t), and the combination of P, Q and f
-// stays in the lane (zfinish in zrow_ops.h).  The kernels that contract or expand y
-// as well apply f to the columns of the plane's spectrum instead, after (forward)
+// stays in the lane (zfinish in zrow_ops.h).  Kernels that contract or expand y as
+// well may apply f to the columns of the plane's spectrum instead, after (forward)
 // or before (inverse) y: fewer values than the rows'.
 //
 // Inverse.  With V = conj(f) Y[k], f Y[-k] and U = V C_t, the row is

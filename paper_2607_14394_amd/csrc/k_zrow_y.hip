@@ -32,7 +32,8 @@ namespace {
 constexpr int kYWaves = 8;
 
 // MODE 2: N_z a multiple of 32, whole units without masks.  ACC: shorter chains
-// of roundings (zrow_ops.h).  Two workgroups a CU where 128 registers hold the
+// of roundings (zrow_ops.h), 1 of the y products alone, 2 of the rows' as well; the
+// phases then go to the columns.  Two workgroups a CU where 128 registers hold the
 // accumulators (one t group, one y tile): 28 channels of 21 x 21 x 28 x 8 19.3 us
 // without ACC, 23.2 with it and 131 registers, 20.8 with it and 128.
 template <int TH, int NT, int MK, int FOLD, int MODE, int NCY, int KYT, int ACC>
@@ -60,9 +61,11 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
   for (int s = 0; s < TH * 4; ++s)
 #pragma unroll
     for (int k = 0; k < MK; ++k) ta[s][k] = timg[(s * MK + k) * 64 + lane];
-  float4 ph[MTW];  // half-position phases of this lane's columns
+  // half-position phases: of this lane's columns (ACC), or of its row modes
+  float4 ph[ACC ? MTW : NT];
 #pragma unroll
-  for (int t = 0; t < MTW; ++t) ph[t] = FOLD ? phase[min(16 * (w + NW * t) + (lane & 15), f.mcols - 1)] : float4{};
+  for (int t = 0; t < (ACC ? MTW : NT); ++t)
+    ph[t] = phase[ACC ? min(16 * (w + NW * t) + (lane & 15), f.mcols - 1) : t * 64 + lane];
 
   const ZLane l = zlane<TH>(a);
   const int m = l.m, g = l.g;
@@ -125,7 +128,7 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
         yr[c][k][t] = v4f{0.f, 0.f, 0.f, 0.f};
         yi[c][k][t] = v4f{0.f, 0.f, 0.f, 0.f};
       }
-  constexpr int ZS = 1 + ACC;
+  constexpr int ZS = ACC == 2 ? 2 : 1;
   v4f R[ZS][NT][TH], I[ZS][NT][TH];
 
   // As fwd_tzy_kernel's process: contract buffer k's unit, refill the buffer,
@@ -143,10 +146,12 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
     zload<TH, FOLD, MODE>(x + row_of(far, &vb[k]) * row_len, a, l, far.u, xb[k]);
     if (!live || c.u != a.units - 1) return;
     float2* vrow = vlds + (c.h * 16 + w + NW * c.j) * f.mrow;
-    zfinish<TH, NT, MK, 0, ACC>(R, I, {}, ta, a, l, [&](int e, v4f_c v, bool both) {
+    const auto put = [&](int e, v4f_c v, bool both) __attribute__((always_inline)) {
       vrow[e] = valid ? make_float2(v[0], v[1]) : make_float2(0.f, 0.f);
       if (both) vrow[e + 1] = valid ? make_float2(v[2], v[3]) : make_float2(0.f, 0.f);
-    });
+    };
+    if constexpr (ACC) zfinish<TH, NT, MK, 0, ACC == 2>(R, I, {}, ta, a, l, put);
+    else zfinish<TH, NT, MK, FOLD, 0>(R, I, ph, ta, a, l, put);
     if (c.h != NCY - 1 || c.j != SPW - 1) return;
     __syncthreads();
     float4 br[NCY][KYT], bi[NCY][KYT];
@@ -222,7 +227,7 @@ fwd_zty_kernel(const float* __restrict__ x, float2* __restrict__ out, const floa
               const int sl = 16 * kk + 4 * g + i;
               const int p = NCY == 2 ? 2 * sl + cl : sl;
               const float2 v = make_float2(yr[cl][kk][t][i], yi[cl][kk][t][i]);
-              if (p < f.ky && mc < f.mcols) op[int64_t(p) * f.mcols + mc] = FOLD ? turn<1>(v.x, v.y, ph[t]) : v;
+              if (p < f.ky && mc < f.mcols) op[int64_t(p) * f.mcols + mc] = ACC ? turn<1>(v.x, v.y, ph[ACC ? t : 0]) : v;
             }
             yr[cl][kk][t] = v4f{0.f, 0.f, 0.f, 0.f};
             yi[cl][kk][t] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -249,7 +254,10 @@ const void* pick_y(const ZRowCfg& c) {
 template <int TH, int NT, int MK>
 const void* pick_fold(const ZRowCfg& c) {
   if (!c.fold) return pick_y<TH, NT, MK, 0, 1, 0>(c);
-  if (c.acc) return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2, 1>(c) : pick_y<TH, NT, MK, 1, 1, 1>(c);
+  if (c.acc == 2) return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2, 2>(c) : pick_y<TH, NT, MK, 1, 1, 2>(c);
+  if constexpr (TH == 1) {
+    if (c.acc) return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2, 1>(c) : pick_y<TH, NT, MK, 1, 1, 1>(c);
+  }
   return c.fmode == 2 ? pick_y<TH, NT, MK, 1, 2, 0>(c) : pick_y<TH, NT, MK, 1, 1, 0>(c);
 }
 // The combinations that plans take (zty_covers in tables.cpp): two t groups

@@ -47,7 +47,10 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
   const int mc = 16 * w + m;
   const bool col_ok = mc < f.mcols;
   float2 u[NCY][JQY][4];
-  const float4 ph = phase[min(mc, f.mcols - 1)];  // the column's half-position phase
+  constexpr int ACC = KG == 2;  // shorter chains (zrow_ops.h): K_t <= 8, where t-first rows fold z into four classes
+  float4 ph[ACC ? 1 : NT];      // half-position phases: of the column (ACC), or of the row modes
+#pragma unroll
+  for (int n = 0; n < (ACC ? 1 : NT); ++n) ph[n] = phase[ACC ? min(mc, f.mcols - 1) : n * 64 + lane];
   {
     const float2* sp = in + pl * int64_t(f.ky) * f.mcols;
 #pragma unroll
@@ -74,18 +77,19 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
   for (int i = threadIdx.x; i < nimg; i += blockDim.x) zl2[i] = zimg[i];
   __syncthreads();
 
-  // (after the staging, so that the spectrum's loads stay in flight across it)
+  if constexpr (ACC) {  // (after the staging, so that the spectrum's loads stay in flight across it)
 #pragma unroll
-  for (int cl = 0; cl < NCY; ++cl)
+    for (int cl = 0; cl < NCY; ++cl)
 #pragma unroll
-    for (int q = 0; q < JQY; ++q)
+      for (int q = 0; q < JQY; ++q)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) u[cl][q][i] = turn<1>(u[cl][q][i].x, u[cl][q][i].y, conj_phase(ph));
+        for (int i = 0; i < 4; ++i) u[cl][q][i] = turn<1>(u[cl][q][i].x, u[cl][q][i].y, conj_phase(ph[0]));
+  }
 
   const int64_t row_len = int64_t(a.nz) * (T32 ? 32 : a.nt);
   for (int gq = q0; gq < q1; ++gq) {
     if (16 * w < f.mcols) {
-      v4f er[NCY], ei[NCY], fr[NCY], fi[NCY];  // products of Re and of Im of the basis (a chain of roundings each)
+      v4f er[NCY], ei[NCY], fr[NCY], fi[NCY];  // ACC: products of Re and of Im of the basis
 #pragma unroll
       for (int cl = 0; cl < NCY; ++cl) {
         er[cl] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -103,14 +107,18 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
             const float2 v = u[cl][q][i];
             er[cl] = mfma(br[i], v.x, er[cl]);
             ei[cl] = mfma(br[i], v.y, ei[cl]);
-            fr[cl] = mfma(bi[i], -v.y, fr[cl]);
-            fi[cl] = mfma(bi[i], v.x, fi[cl]);
+            v4f& r = ACC ? fr[cl] : er[cl];
+            v4f& s = ACC ? fi[cl] : ei[cl];
+            r = mfma(bi[i], -v.y, r);
+            s = mfma(bi[i], v.x, s);
           }
         }
+      if constexpr (ACC) {
 #pragma unroll
-      for (int cl = 0; cl < NCY; ++cl) {
-        er[cl] += fr[cl];
-        ei[cl] += fi[cl];
+        for (int cl = 0; cl < NCY; ++cl) {
+          er[cl] += fr[cl];
+          ei[cl] += fi[cl];
+        }
       }
       // accumulator register i holds slot 4g + i, column mc
 #pragma unroll
@@ -132,7 +140,8 @@ inv_yzrow_kernel(const float2* __restrict__ in, float* __restrict__ y, const flo
         float2 un[NT][KG][2];
         zinv_load<NT, KG>(vlds + (h * 16 + w) * f.mrow, a, m, g, un);
         v4f A[NT][TH], B[NT][TH];
-        zinv_t<TH, NT, KG, 0>(un, {}, tb, a, m, g, A, B);
+        if constexpr (ACC) zinv_t<TH, NT, KG, 0>(un, {}, tb, a, m, g, A, B);
+        else zinv_t<TH, NT, KG, 1>(un, ph, tb, a, m, g, A, B);
         zinv_z<TH, NS, 1, T32>(A, B, zl2, a, m, g, y + (int64_t(pl) * f.ny + s + h * f.half) * row_len);
       }
     }

@@ -102,7 +102,11 @@ bool z_first(const StreamCfg& s, bool whole_z, ZRowCfg* out) {
   z.steps = static_cast<int>(ceil_div(z.np, 4));
   z.units = static_cast<int>(ceil_div(z.np, 16));
   z.fmode = z.fold && s.nz % 32 == 0 ? 2 : 1;
-  z.acc = s.ncls > 1 ? 1 : 0;
+  // Where the t-first rows fold z their chains are short, and so are these rows'
+  // (zrow_ops.h) unless the y chains alone make up for them: one t group and one
+  // unit of z (layer of 32^3 x 8: error 2.5e-7 and 28.9 us, with both 2.4e-7 and
+  // 29.7, with neither 2.7e-7 and 28.9; t first 2.5e-7).
+  z.acc = s.ncls == 1 ? 0 : (z.th == 1 && z.units == 1 ? 1 : 2);
   // z bases in LDS, four workgroups a CU
   if (z.units * size_t(z.ntl) * 2 * 64 * 16 > 40 * 1024 || z.units * size_t(z.ns) * 64 * 8 > 40 * 1024) return false;
   *out = z;
