@@ -44,14 +44,15 @@ namespace {
 // TH: t groups; NT: 16-mode tiles of k = 0 .. kmax; MK: 1 when K_t <= 8 (Br
 // and Bi rows in one tile), else 2; ACC: shorter chains (zrow_ops.h).
 //
-// (ACC with two t groups: three waves per SIMD, its accumulators would spill at
-// four: 5 channels of 34 x 239 x 126 x 21 323 us at four, 193 at three, 258 without
-// ACC.)
+// Three waves per SIMD where the accumulators would spill at four (two t groups
+// with two k_t tiles or ACC: 5 channels of 34 x 239 x 126 x 21 193 us at three, 323
+// at four; 10 of 17 x 40 x 191 x 32, K_t 13, 56 and 74).
+//
 // Every wave walks its (row, unit) pairs with NB unit buffers, loads are
 // unconditional and past the last unit re-read the last row, as in
 // fwd_tz_body: the waits for one unit then cover that unit's loads only.
 template <int TH, int NT, int MK, int FOLD, int MODE, int ACC>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 && !(ACC && TH == 2) ? 4 : 3)))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT == 1 && !(TH == 2 && (ACC || MK == 2)) ? 4 : 3)))
 fwd_zrow_kernel(const float* __restrict__ x, float2* __restrict__ out, const float4* __restrict__ zimg,
                 const float4* __restrict__ phase, const float* __restrict__ timg, ZRowArgs a) {
   constexpr int NB = kZBufs;
