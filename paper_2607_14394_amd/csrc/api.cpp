@@ -179,7 +179,7 @@ dtst_status run_forward_chain(const dtst_plan_st* p, int64_t channels, const flo
                                   p->blob + im.y_fwd, stream);
     });
     if (e != hipSuccess) return device_status(e, "z+t+y contraction launch");
-  } else if (dv.sc.fuse_y && !dv.zr.fwd) {
+  } else if (dv.sc.fuse_yf && !dv.zr.fwd) {
     e = timed(K_FWD_TZY, stream, [&] {
       return dtst::launch_fwd_tzy(dv.sc, dv.ay_f, x, w2, planes, static_cast<int>(dv.d.n_local[1]), timg,
                                   p->blob + dv.img.z_fwd, p->blob + dv.img.y_fwd, stream);
@@ -305,13 +305,13 @@ dtst_status dtst_desc_schedule(const dtst_desc* d, uint32_t flags, dtst_schedule
   std::string err;
   const dtst_status s = dtst::derive(d, flags, &dv, &err);
   if (s != DTST_OK) return fail(s, err);
-  // (the chains below choose their kernels by the same three fields)
-  auto rows = [&](int z_first) {
+  // (the chains choose their kernels by the same fields)
+  auto rows = [&](int z_first, int fuse_y) {
     if (z_first) return z_first == 2 ? DTST_ROWS_Z_FIRST_Y : DTST_ROWS_Z_FIRST;
-    return dv.sc.fuse_y ? DTST_ROWS_T_FIRST_Y : DTST_ROWS_T_FIRST;
+    return fuse_y ? DTST_ROWS_T_FIRST_Y : DTST_ROWS_T_FIRST;
   };
-  out->forward = rows(dv.zr.fwd);
-  out->inverse = rows(dv.zr.inv);
+  out->forward = rows(dv.zr.fwd, dv.sc.fuse_yf);
+  out->inverse = rows(dv.zr.inv, dv.sc.fuse_y);
   out->block = dv.blk == 2 ? DTST_BLOCK_ROW_TASKS : (dv.blk ? DTST_BLOCK_CHUNKS : DTST_BLOCK_SEPARATE);
   out->z_classes = dv.sc.ncls;
   out->t_folded = dv.sc.tf;

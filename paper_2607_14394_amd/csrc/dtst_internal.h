@@ -48,7 +48,8 @@ struct StreamCfg {
   //   fused_mrow LDS row stride (complex values) of the exchanged row results
   //   fused_y_lds 1 when the y basis images are staged in LDS (else read from
   //              global memory)
-  int fuse_y = 0, ncy = 1, kyt = 1, fused_mrow = 0, fused_y_lds = 0;
+  //   fuse_yf    whether the t-first forward takes it too (fuse_y: the inverse)
+  int fuse_y = 0, fuse_yf = 0, ncy = 1, kyt = 1, fused_mrow = 0, fused_y_lds = 0;
   size_t fused_lds_bytes = 0;
   // filled at plan creation on the plan's device (prepare_stream)
   int grid_fwd = 0, grid_inv = 0;  // resident workgroups of each kernel

@@ -336,6 +336,11 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   const bool has_w1 = !sc.fuse_y || sc.nt % 4 != 0;
   dv.w1_bytes = has_w1 ? w1 : 0;
   dv.ws_bytes = dv.w1_bytes + w2;
+  // At N_t % 4 != 0 the fused forward's masked tiles cost it more than the W1
+  // traffic it saves: 8 channels, B = 3, 26 x 19 rows of 210 x 30 155 us, separate
+  // 97; 12 of 45 x 129 rows of 26 x 30 113 and 74; 24, B = 2, 21 x 41 of 29 x 26 49
+  // and 48.
+  sc.fuse_yf = sc.fuse_y && !has_w1 ? 1 : 0;
 
   // ---- z-first rows ----
   // Taken where they need fewer matrix instructions than the t-first kernels;
@@ -428,7 +433,7 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   expand_parts(dv.ax_i);
   expand_parts(dv.ay_i);
   dv.ay_b = dv.ay_i;
-  if (dv.zr.fwd == 2 || (dv.zr.fwd == 0 && sc.fuse_y)) dv.ay_f.parts = 2;
+  if (dv.zr.fwd == 2 || (dv.zr.fwd == 0 && sc.fuse_yf)) dv.ay_f.parts = 2;
   if (dv.zr.inv == 2 || (dv.zr.inv == 0 && sc.fuse_y)) dv.ay_i.parts = 2;
 
   // ---- fused inverse z + t expansion and block epilogue ----

@@ -43,6 +43,15 @@ def test_z_first_cases_cover_the_unfolded_fused_forward():
     assert seen == {(1, 1, False), (1, 1, True), (2, 1, False), (2, 1, True), (2, 2, False), (2, 2, True)}
 
 
+def test_t_first_forward_is_fused_at_whole_quads_of_t():
+    """N_t % 4 == 0: y in the t-first forward's launch; otherwise launches of its own (the inverse stays fused)."""
+    for nt, way in ((28, D.ROWS_T_FIRST_Y), (30, D.ROWS_T_FIRST)):
+        n = (52, 76, 38, nt)
+        s = schedule((n, (26, 19) + n[2:], (0, 0, 0, 0), (22, 12, 16), 4, 3, 8, 8))
+        assert s.forward == way
+        assert s.inverse in (D.ROWS_T_FIRST_Y, D.ROWS_Z_FIRST_Y)
+
+
 @pytest.mark.parametrize("case", ROW_BLOCKS, ids=str)
 def test_row_block_cases(case):
     ng, kz, kt, ci, co, shard = case
