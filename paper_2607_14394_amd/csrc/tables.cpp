@@ -356,17 +356,24 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     z.fused_lds_bytes = size_t(dv.ay_f.ktiles) * dv.ay_f.JQ * 2 * 64 * 16 + size_t(16) * z.ncy * z.fused_mrow * 8 +
                         size_t(z.units) * z.ntl * 2 * 64 * 16;
     const bool fwd_better = z_first_fwd_cost(z) < tcost;
-    // Separate launches stay where the fused kernel's two waves per SIMD do not
-    // carry the row work: two mode tiles (28 x 24 x 86 x 32, K_z 36: 245 us
-    // separate, 283 fused) or one t group (99 x 90 x 75 x 10: 289, 333); with
-    // one tile and two groups fused was faster (32 x 128 x 128 x 32, K_z 16:
-    // 445 and 324; 42 x 138 x 52 x 32: 147 and 118; 12 x 20 x 108 x 32: 34 and
-    // 28).  A plan whose workspace
+    // Separate launches (where the plan has W1) stay where the fused kernel's two
+    // waves per SIMD do not carry the row work: two mode tiles (28 x 24 x 86 x 32,
+    // K_z 36: 86 us separate), or one t group (99 x 90 x 75 x 10: 289, fused 333);
+    // with one tile and two groups fused was faster (32 x 128 x 128 x 32, K_z 16:
+    // 355 and 287; 32 x 128 x 64 x 30: 206 and 176) unless the last group of 16 y
+    // slots leaves over a quarter of the slots empty (of 90 random geometries the
+    // 19 such were 11% faster separate, 18 x 18 x 187 x 28 54 and 71, the others 1%
+    // slower); rows of four z classes stay fused there too, for its shorter z chains
+    // (16 x 16 x 148 x 26: 2.0e-7, separate 2.2e-7, t first 2.0e-7).  With one t group and the y contraction in the t-first kernel's
+    // reach, rows z first in separate launches were faster than t first fused (45
+    // geometries of N_t 5 to 15: 1.56 times, 0.98 to 5.1).  A plan whose workspace
     // has no W1 (fused t-first kernels otherwise) stays fused.
+    const int64_t slots = fold_y ? d->n_local[1] / 2 : d->n_local[1];
     const bool zty_covers = z.th == 2 ? z.ntl == 1 : z.mk == 1;  // (the instances there are)
     const bool fused = (flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && zty_covers && mcols <= 256 && dv.K[1] <= 32 &&
                        z.kyt <= (fold_y ? 1 : 2) && z.fused_lds_bytes <= 160 * 1024 &&
-                       bc * d->n_local[0] < (1 << 24) && (!has_w1 || (z.ntl == 1 && z.th == 2));
+                       bc * d->n_local[0] < (1 << 24) &&
+                       (!has_w1 || (z.ntl == 1 && z.th == 2 && (z.acc || slots * 4 >= dv.ay_f.JQ * 16 * 3)));
     if (fwd_better && fused) {
       z.fwd = 2;
       // A workgroup fills a CU (of 256): the parts that leave the fewest slot

@@ -6,7 +6,7 @@ import pytest
 D = pytest.importorskip("paper_2607_14394_amd", reason="libdtst.so not built")
 
 from test_gpu_t_chunks import ROW_BLOCKS  # noqa: E402
-from test_gpu_z_first import CASES, T_FIRST  # noqa: E402
+from test_gpu_z_first import CASES, FUSED, T_FIRST, fused_case  # noqa: E402
 
 
 def schedule(case, flags=0):
@@ -43,6 +43,24 @@ def test_z_first_cases_cover_the_unfolded_fused_forward():
     assert seen == {(1, 1, False), (1, 1, True), (2, 1, False), (2, 1, True), (2, 2, False), (2, 2, True)}
 
 
+def test_fused_cases_cover_the_mirrored_fused_forward():
+    """Each (t groups, K_t tiles, y folded, whole units, z classes of the t-first rows) with mirrored rows, and with
+    one t group and several classes one unit and more."""
+    seen = set()
+    for case in FUSED:
+        c = fused_case(case)
+        s = schedule(c)
+        assert s.forward == D.ROWS_Z_FIRST_Y and s.z_mirrored, case
+        ng, nl, _, _, kt = c[:5]
+        seen.add((1 if nl[3] <= 16 else 2, 1 if kt <= 8 else 2, nl[1] == ng[1] and ng[1] % 2 == 0, ng[2] % 32 == 0,
+                  s.z_classes > 1))
+        if nl[3] <= 16 and s.z_classes > 1:
+            seen.add(("one unit" if ng[2] <= 32 else "units", nl[1] % 2 == 0, ng[2] % 32 == 0))
+    flags = [(y, w, c) for y in (False, True) for w in (False, True) for c in (False, True)]
+    assert seen == ({(th, mk) + f for th, mk in ((1, 1), (2, 1), (2, 2)) for f in flags}
+                    | {(u, y, w) for u in ("one unit", "units") for y in (False, True) for w in (False, True)})
+
+
 def test_t_first_forward_is_fused_at_whole_quads_of_t():
     """N_t % 4 == 0: y in the t-first forward's launch; otherwise launches of its own (the inverse stays fused)."""
     for nt, way in ((28, D.ROWS_T_FIRST_Y), (30, D.ROWS_T_FIRST)):
@@ -50,6 +68,14 @@ def test_t_first_forward_is_fused_at_whole_quads_of_t():
         s = schedule((n, (26, 19) + n[2:], (0, 0, 0, 0), (22, 12, 16), 4, 3, 8, 8))
         assert s.forward == way
         assert s.inverse in (D.ROWS_T_FIRST_Y, D.ROWS_Z_FIRST_Y)
+
+
+def test_z_first_forward_with_empty_y_slots():
+    """Over a quarter of the last group's 16 y slots empty: y in launches of its own, unless the plan has no W1
+    (N_t = 32, fused t-first kernels) or the rows form shorter chains (four z classes)."""
+    for n, k, way in (((18, 18, 187, 28), (5, 8, 10), D.ROWS_Z_FIRST), ((18, 24, 187, 28), (5, 8, 10), D.ROWS_Z_FIRST_Y),
+                      ((16, 16, 148, 26), (6, 7, 4), D.ROWS_Z_FIRST_Y)):
+        assert schedule((n, n, (0, 0, 0, 0), k, 3, 1, 4, 4)).forward == way, n
 
 
 @pytest.mark.parametrize("case", ROW_BLOCKS, ids=str)
