@@ -485,7 +485,14 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     // 7 of 5940 of 103 x 32: 493 -> 374; 12 of 1232 of 114 x 8: 110 -> 83);
     // above that the bypass on the vector unit is the slower one (10 channels
     // of 2184 rows of 42 x 32: 110 -> 136; 16 of 558 of 137 x 8: 88 -> 108).
-    if (dv.blk && (d->c_in <= 8 || (d->c_in <= 12 && sc.th == 1)) && block_row_supported(dv.zr, d->c_in, d->c_out))
+    // So they are for rows short for more than 8 output channels, N_z N_t below 40
+    // sqrt(C_in C_out) (16 x 65 rows of 16 x 32, 8 -> 30 channels: 76 -> 156; 18
+    // such of 294 random blocks: 0.42 to 1.05 of the chunks' rate, but for one of
+    // 1.7; 8 or fewer: 26 x 8, 6 channels, 41 -> 28).
+    const int64_t row = int64_t(sc.nz) * sc.nt;
+    const bool filled = d->c_out <= 8 || row * row >= int64_t(1600) * d->c_in * d->c_out;
+    if (dv.blk && (d->c_in <= 8 || (d->c_in <= 12 && sc.th == 1)) && filled &&
+        block_row_supported(dv.zr, d->c_in, d->c_out))
       dv.blk = 2;
     dv.blk_w1_bytes = dv.blk ? w1 : dv.w1_bytes;
     dv.blk_ws_bytes = dv.blk ? w1 + w2 : dv.ws_bytes;

@@ -142,7 +142,13 @@ ROW_BLOCKS = [((2, 3, 204, 16), 19, 4, 5, 5, None), ((3, 7, 27, 8), 13, 3, 4, 4,
               ((9, 40, 50, 32), 6, 9, 2, 5, None)]
 
 
-@pytest.mark.parametrize("case", ROW_BLOCKS, ids=lambda c: "x".join(map(str, c[0])) + f"_c{c[3]}_{c[4]}")
+# few input channels, and rows too short for their output channels to be row tasks: chunks
+SHORT_ROWS = [((4, 13, 16, 32), 7, 7, 8, 30, None), ((3, 11, 20, 10), 8, 4, 9, 32, None),
+              ((4, 7, 14, 20), 5, 7, 4, 20, None), ((2, 9, 16, 8), 5, 3, 1, 32, None),
+              ((2, 9, 25, 12), 4, 3, 6, 17, (11, 9))]
+
+
+@pytest.mark.parametrize("case", ROW_BLOCKS + SHORT_ROWS, ids=lambda c: "x".join(map(str, c[0])) + f"_c{c[3]}_{c[4]}")
 def test_inverse_block_few_channels(case):
     """One to three tiles of input channels, one and two mode tiles, ragged and few z positions, a z shard, fewer
     and more rows than a launch keeps resident."""

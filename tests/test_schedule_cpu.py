@@ -5,7 +5,7 @@ import pytest
 
 D = pytest.importorskip("paper_2607_14394_amd", reason="libdtst.so not built")
 
-from test_gpu_t_chunks import ROW_BLOCKS  # noqa: E402
+from test_gpu_t_chunks import ROW_BLOCKS, SHORT_ROWS  # noqa: E402
 from test_gpu_z_first import CASES, FUSED, T_FIRST, fused_case  # noqa: E402
 
 
@@ -78,12 +78,12 @@ def test_z_first_forward_with_empty_y_slots():
         assert schedule((n, n, (0, 0, 0, 0), k, 3, 1, 4, 4)).forward == way, n
 
 
-@pytest.mark.parametrize("case", ROW_BLOCKS, ids=str)
+@pytest.mark.parametrize("case", ROW_BLOCKS + SHORT_ROWS, ids=str)
 def test_row_block_cases(case):
     ng, kz, kt, ci, co, shard = case
     off, nz = shard if shard else (0, ng[2])
     s = schedule((ng, (ng[0], ng[1], nz, ng[3]), (0, 0, off, 0), (1, 1, kz), kt, 2, ci, co))
-    assert s.block == D.BLOCK_ROW_TASKS
+    assert s.block == (D.BLOCK_ROW_TASKS if case in ROW_BLOCKS else D.BLOCK_CHUNKS)
 
 
 # (n, k_max z, k_t, C_in, C_out), fused: blocks whose folded z image leaves the chunked kernel too little LDS
