@@ -239,8 +239,8 @@ __device__ __forceinline__ float sum_rows_to_row(float r0, float r1, float r2, f
 // ZP: z tiles per chunk.  Two t groups fill a chunk of one tile (512 points at
 // N_t = 32, one 64-point group per wave); with N_t <= 16 one tile left half of
 // the waves without points and paid a barrier for half the work (18 channels of
-// 2288 rows of 25 x 8, with the x and y expansions: 100 us, with two tiles 80; 16
-// of 558 of 137 x 8: 89, with four 82; one class only, see z_tiles).
+// 2288 rows of 25 x 8, with the x and y expansions: 100 us, with two tiles 80;
+// see z_tiles for where they pay).
 template <int CT, int TH, int MT, int NCLS, int TF, int T32, int ZP, int KI, int OT, int SPF, int XD, int OH>
 __global__ void __launch_bounds__(64 * kBlkWaves)
 inv_zt_block_kernel(const float2* __restrict__ in, const float* __restrict__ x, const float* __restrict__ wb,

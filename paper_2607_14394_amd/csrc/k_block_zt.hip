@@ -28,12 +28,27 @@ size_t lds_bytes(const StreamCfg& c, int64_t ci, int64_t co, int zp) {
          2 * size_t(cb) * 16 * zp * c.nt * sizeof(float);
 }
 
-// z tiles per chunk: as many as give the 8 waves points (16 ZP N_t <= 512), the
-// row has and the LDS holds; one with two t groups, and with two z classes (the
-// runs' expansions kept for the second class spilled: 28 channels of 981 rows of
-// 46 x 16 137 -> 147 us).
+// z tiles per chunk.  More of them fill the 8 waves with points (16 ZP N_t <=
+// 512) and halve the barriers, but the last chunk of a row then runs empty tiles,
+// and channels above 20 make two passes a chunk as it is.  Against one tile, over
+// 220 random blocks of one z class: N_t > 8, two tiles, an even number of tiles a
+// row and up to 20 channels 1.00 to 1.10 times (22 x 16, 14: 0.93; 76 x 12, 16:
+// 1.09), other rows 0.77 to 1.02 (78 x 236 rows of 35 x 12, 14 channels: 0.90;
+// 66 x 26 of 101 x 16, 24: 0.89).  N_t <= 8, two: 1.0 to 1.36 (16 channels of 18 x 31
+// rows of 137 x 8: 1.16), three tiles a row 0.78 to 1.06.  Four: above two only at N_t <= 6
+// with up to 20 channels and chunks nearly full (40 x 48 rows of 111 x 4: 1.26,
+// four 1.54; 60 x 6: 1.32, 1.39; 119 x 8: 1.24, 1.13).  One with two t groups, and
+// with two z classes (the runs' expansions kept for the second class spilled: 28
+// channels of 981 rows of 46 x 16 137 -> 147 us).
 int z_tiles(const StreamCfg& c, int64_t ci, int64_t co) {
-  int zp = c.th == 2 || c.nt > 16 || c.ncls == 2 ? 1 : (c.nt > 8 || c.ct == 2 ? 2 : 4);
+  if (c.th == 2 || c.nt > 16 || c.ncls == 2) return 1;
+  const bool few = kio_of(ci, co) < 2;
+  int zp = 1;
+  if (c.nt > 8) {
+    if (few && c.zt % 2 == 0) zp = 2;
+  } else if (c.zt != 3) {
+    zp = c.nt <= 6 && few && (c.zt + 1) % 4 <= 1 ? 4 : 2;
+  }
   while (zp > 1 && (zp > c.zt || lds_bytes(c, ci, co, zp) > 160 * 1024)) zp /= 2;
   return zp;
 }

@@ -135,6 +135,28 @@ def test_pointwise_and_epilogue(points):
     plan.close()
 
 
+@pytest.mark.parametrize("c", [14, 24])
+@pytest.mark.parametrize("nt,nz", [(4, 17), (4, 111), (6, 24), (6, 50), (6, 64), (8, 40), (8, 75), (8, 137), (12, 35),
+                                   (12, 60), (16, 90), (16, 112)])
+def test_inverse_block_z_runs(nt, nz, c):
+    """One t group, one z class: chunks of one, two and four z tiles, whole and ragged last ones and rows of fewer."""
+    torch = torch_gpu()
+    import paper_2607_14394_amd as D
+    n = (2, 3, nz, nt)
+    g = geometry(n, n, (0, 0, 0, 0), (1, 1, 5), 3, 2, c, c)
+    assert D.dtst_desc_schedule(desc_of(g)).block == D.BLOCK_CHUNKS
+    say(f"[t chunks, z runs] n={n} c={c}")
+    plan = D.Plan(desc_of(g))
+    yh, x = rand_cplx((2, c) + g.K, 51), rand_real((2, c) + n, 52)
+    wb = (rand_real((c, c), 53) / np.sqrt(c)).astype(np.float32)
+    y = Guarded(torch, plan.spatial_shape(c), torch.float32)
+    plan.inverse_block(dev(torch, yh), dev(torch, x), dev(torch, wb), y.t)
+    torch.cuda.synchronize()
+    check(np_of(y.t), O.block_epilogue(x, wb, O.inverse(yh, g)), "inverse + block epilogue")
+    assert y.guards_intact()
+    plan.close()
+
+
 # (n, k_max z, k_t, C_in, C_out, shard): row tasks of few input channels
 ROW_BLOCKS = [((2, 3, 204, 16), 19, 4, 5, 5, None), ((3, 7, 27, 8), 13, 3, 4, 4, None),
               ((2, 5, 36, 32), 13, 5, 7, 7, None), ((2, 3, 30, 30), 8, 16, 8, 32, None),
