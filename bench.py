@@ -145,7 +145,7 @@ def work(g, channels, m_count=None, acc_share=0.0):
     # rows with z contracted first (t expanded first): the real row against cosines and sines of half
     # the modes (X[-k] is the conjugate of X[k]) over half the z rows, then t by four real products
     # for both of a pair of modes
-    z_fold = 2 if _folded(g, 2) else 1
+    z_fold = 2 if _schedule(g).z_mirrored else 1
     z_rows = rows * (2 * Kz * Nz * Nt / z_fold + 4 * Kz * Kt * Nt)
     for role, first in zip(("stream_fwd_tz", "stream_inv_zt"), _z_first(g)):
         if first:
@@ -174,8 +174,9 @@ def _block_zt_work(g):
     Kz, Kt = 2 * g["kmax"][2], g["kt"]
     V = _vol(g)
     sf = stage_flops(g, co)
-    zc = _block_z_classes(g)
-    tc = _t_classes(g)
+    s = _schedule(g)
+    zc = s.block_z_classes
+    tc = 2 if s.block_t_folded else 1
     byp = 2 * B * V * ci * co
     return dict(bytes=B * co * Nx * Ny * Kz * Kt * 8 + B * (ci + co) * V * 4, flops=sf["t"] + sf["z"] + byp,
                 mfma_flops=sf["t"] / tc + sf["z"] / zc * (0.75 if tc == 2 else 1.0) + byp)
@@ -204,70 +205,27 @@ def _axis_classes(g, dim):
     return 4 if g["n_global"][dim] % 4 == 0 and K % 64 == 0 and K <= 128 else 2
 
 
+def _schedule(g):
+    """The kernels that the library takes for g (dtst_desc_schedule)."""
+    import paper_2607_14394_amd as D
+    return D.dtst_desc_schedule(g)
+
+
 def _t_classes(g):
-    """2 when the streaming kernels fold t (8 < k_t <= 16 and the whole even
-    16 < N_t <= 32 local: even k_t from the sums of t and t + N_t/2, odd k_t from
-    the differences), else 1; the t MFMA work divides by it."""
-    nt = g["n_local"][3]
-    return 2 if 8 < g["kt"] <= 16 and 16 < nt <= 32 and nt % 2 == 0 and g["n_global"][3] == nt else 1
+    """2 when the t-first rows fold t, else 1; the t MFMA work divides by it."""
+    return 2 if _schedule(g).t_folded else 1
 
 
 def _z_classes(g):
-    """z mode classes of the streaming kernels.  z folds only where the shard
-    holds the whole even N_z; the class count is the one with the fewest
-    padded slots per class (the z products per row are those slots x N_z for
-    any count), the smaller one on a tie: 4 (k mod 4: N_z % 4 == 0, even
-    k_max, and at most 16 modes per class with k_t > 8 or 8 with k_t <= 8),
-    2 (parity) or 1.  The z MFMA work divides by it."""
-    if not _folded(g, 2):
-        return 1
-    Kz = 2 * g["kmax"][2]
-    ct = 2 if g["kt"] > 8 else 1
-
-    def padded(n):
-        if n == 4 and ct == 1:
-            return 8
-        k = -(-(-(-Kz // n)) // 16) * 16
-        return 64 if k == 48 else k
-
-    n = 1
-    if padded(2) < padded(n):
-        n = 2
-    four = g["n_global"][2] % 4 == 0 and g["kmax"][2] % 2 == 0 and Kz <= (64 if ct == 2 else 32)
-    if four and padded(4) < padded(n):
-        n = 4
-    return n
+    """z mode classes of the t-first rows (1, 2: parity, 4: k mod 4); the z MFMA work divides by it."""
+    return _schedule(g).z_classes
 
 
 def _z_first(g):
-    """Whether the stream kernels contract z before t (forward) and expand t
-    before z (inverse): the library's rule, fewer matrix instructions a row
-    than with t first."""
-    Kz, kt, Nz, Nt = 2 * g["kmax"][2], g["kt"], g["n_local"][2], g["n_local"][3]
-    cdiv = lambda a, b: -(-a // b)
-    th, ct, tf, n = cdiv(Nt, 16), 2 if kt > 8 else 1, _t_classes(g) == 2, _z_classes(g)
-    modes = Kz // 2 + 1
-    if Nt < 4 or th > 2 or modes > 32:
-        return False, False
-    slots = 8 if n == 4 and ct == 1 else 16 * cdiv(cdiv(Kz, n), 16)
-    mt = (64 if slots == 48 else slots) // 8
-    t_first = cdiv(cdiv(Nz, n), 16) * n * (th * 4 * ct // (2 if tf else 1) + (3 * mt // 2 if tf else mt * ct) * 4)
-    np_ = cdiv(Nz, 2) if g["n_local"][2] == g["n_global"][2] else Nz
-    ns = max(2, cdiv(modes, 4))
-    ns = ns if ns <= 4 else cdiv(ns, 2) * 2
-    mk = 1 if kt <= 8 else 2
-    fwd = cdiv(modes, 16) * 2 * th * (cdiv(np_, 4) + 4 * mk)
-    inv = 2 * th * (cdiv(np_, 16) * ns + cdiv(ns, 4) * 4 * mk)
-    return fwd < t_first, inv < t_first
-
-
-def _block_z_classes(g):
-    """z classes of the fused inverse + block epilogue kernel: 2 where z folds
-    and the parity classes pad to fewer slots than one class, else 1."""
-    if not _folded(g, 2):
-        return 1
-    Kz = 2 * g["kmax"][2]
-    return 2 if -(-(-(-Kz // 2)) // 16) < -(-Kz // 16) else 1
+    """Whether the stream kernels contract z before t (forward) and expand t before z (inverse)."""
+    import paper_2607_14394_amd as D
+    s = _schedule(g)
+    return s.forward >= D.ROWS_Z_FIRST, s.inverse >= D.ROWS_Z_FIRST
 
 
 def _sha(path):

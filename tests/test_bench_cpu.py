@@ -134,3 +134,25 @@ def test_work_uses_stage_flops_and_folds():
     wa = bench.work(g, 32, acc_share=1.0)
     spec = g["batch"] * 32 * 32 * 32 * 32 * 8 * 8
     assert wa["axis_fwd_x"]["bytes"] - w["axis_fwd_x"]["bytes"] == spec
+
+
+def test_work_follows_the_library_schedule():
+    """Products are counted for the kernels that a plan takes: t unfolded where the folded z image would exceed the
+    LDS, z first with mirrored rows, and z first on a shard of z."""
+    import bench
+    import paper_2607_14394_amd as D
+
+    def g(n, k, kt, nz=None):
+        return dict(n_global=n, n_local=n[:2] + (nz or n[2], n[3]), offset=(0, 0, 0, 0), kmax=k, kt=kt, batch=1,
+                    c_in=4, c_out=4)
+
+    long_z = g((2, 4, 896, 28), (1, 1, 32), 9)
+    s, sf = D.dtst_desc_schedule(long_z), bench.stage_flops(long_z, 4)
+    assert s.forward == D.ROWS_T_FIRST and not s.t_folded
+    assert bench.work(long_z, 4)["stream_fwd_tz"]["mfma_flops"] == sf["t"] + sf["z"] / s.z_classes
+    rows = 4 * 32 * 32
+    for case, fold in ((g((32, 32, 32, 8), (8, 8, 8), 4), 2), (g((32, 32, 56, 16), (8, 8, 4), 8, 41), 1)):
+        assert D.dtst_desc_schedule(case).forward >= D.ROWS_Z_FIRST
+        nz, nt, kz, kt = case["n_local"][2], case["n_local"][3], 2 * case["kmax"][2], case["kt"]
+        assert (bench.work(case, 4)["stream_fwd_tz"]["mfma_flops"]
+                == rows * (2 * kz * nz * nt / fold + 4 * kz * kt * nt))
