@@ -137,20 +137,23 @@ dtst_status dtst_basis_host(const dtst_desc* d, int dim, int kind, float* out, s
  * bound to that device.  On success *out receives the plan.
  *
  * The plan also fixes the kernel schedule of both chains (dtst_forward and
- * dtst_inverse_adj; dtst_inverse and dtst_forward_adj): where the shapes
- * allow it (K_t <= 8, at most 16 z modes per fold class, 4 <= N_t^loc <= 32,
- * K_y <= 32, K_z K_t <= 256; K_t up to 16 where z is contracted before t) the
- * t, z and y contractions run as one launch; otherwise t + z and y are
- * separate launches.  Same as dtst_plan_ex(d, 0, out). */
+ * dtst_inverse_adj; dtst_inverse and dtst_forward_adj): whether a row
+ * contracts t or z first, by which needs fewer products, and whether the t, z
+ * and y contractions run as one launch.  That takes 4 <= N_t^loc <= 32, K_y <=
+ * 32, K_z K_t <= 256, tables within the LDS and, with t first, K_t <= 8 and at
+ * most 16 z modes per fold class (forward: N_t^loc a multiple of 4), or, with z
+ * first, k_max(z) <= 31; elsewhere, and where it was measured faster,
+ * t + z and y are separate launches.  dtst_desc_schedule tells which.  Same as
+ * dtst_plan_ex(d, 0, out). */
 dtst_status dtst_plan(const dtst_desc* d, dtst_plan_t* out);
 
 /* Plan options (bit flags of dtst_plan_ex / dtst_desc_workspace_bytes_ex). */
 enum {
   /* Keep the t + z and y contractions (and the y and z + t expansions) as
    * separate launches even where the shapes allow one launch.  The result
-   * agrees with the default schedule to rounding (the contraction order of
-   * Sec. V-B is the same); the workspace then also holds the (.., N_x, N_y,
-   * K_z, K_t) intermediate. */
+   * agrees with the default schedule to rounding (rows contract t or z first by
+   * the same rule); the workspace then also holds the (.., N_x, N_y, K_z, K_t)
+   * intermediate. */
   DTST_PLAN_SPLIT_SCHEDULE = 1u,
   /* Run dtst_inverse_block as the inverse followed by a separate epilogue
    * launch (the form of dtst_inverse + dtst_block_epilogue) instead of the
@@ -176,7 +179,8 @@ dtst_status dtst_plan_info(dtst_plan_t p, int64_t* n_modes, size_t* workspace_by
  *   xhat[b,c,k] (+)= sum_{n in shard} x[b,c,n] prod_i B_i[k_i, n_i]
  * for the C_in channels.  accumulate = 0 overwrites xhat; 1 adds to it, so
  * calling it for every shard in turn forms the sum of Eq. (dtst_reduce).
- * The contraction order is t, z, y, x (Algorithm 1). */
+ * The contraction order is t, z, y, x (Algorithm 1), or z, t, y, x where rows
+ * contract z first (dtst_desc_schedule). */
 dtst_status dtst_forward(dtst_plan_t p, const float* x, void* xhat, int accumulate,
                          void* workspace, size_t workspace_bytes, void* stream);
 
@@ -193,7 +197,7 @@ dtst_status dtst_mix(dtst_plan_t p, const void* xhat, const void* w_shard, void*
 /* Inverse partial DFT onto the shard (Sec. V-A Eq. dtst_inverse, half
  * spectrum in t) for the C_out channels:
  *   y[b,c,n] = (1/prod N) Re sum_k w(k_t) yhat[b,c,k] conj(prod_i B_i[k_i, n_i]).
- * Expansion order x, y, z, t. */
+ * Expansion order x, y, z, t, or x, y, t, z where rows expand t first. */
 dtst_status dtst_inverse(dtst_plan_t p, const void* yhat, float* y,
                          void* workspace, size_t workspace_bytes, void* stream);
 
@@ -244,14 +248,14 @@ dtst_status dtst_block_epilogue(dtst_plan_t p, const float* x, const float* w_by
  * followed by the block epilogue,
  *   y = GELU( w_bypass x + inverse(yhat) ),
  * with the arrays, layouts, alignment and overlap rules of dtst_inverse and
- * dtst_block_epilogue.  Where the plan allows it (N_t^loc even and at most 32,
+ * dtst_block_epilogue.  Where the plan allows it (N_t^loc even, 4 to 32,
  * N_z^loc N_t^loc per z class a multiple of 4, C_in and C_out at most 32, at
  * most 32 z modes per fold class, the per-workgroup buffers within the LDS; see
- * dtst_plan_block_workspace_bytes) the z and t expansions and the epilogue
+ * dtst_plan_block_info) the z and t expansions and the epilogue
  * run as one kernel that writes y once and reads x once; otherwise, or with
  * DTST_PLAN_UNFUSED_BLOCK, the inverse and the epilogue are enqueued one
  * after the other.  The workspace must hold
- * dtst_plan_block_workspace_bytes(p) bytes (DTST_ERR_INVALID_ARG otherwise);
+ * the bytes that dtst_plan_block_info gives (DTST_ERR_INVALID_ARG otherwise);
  * it is scratch, owned by the caller.  Asynchronous on `stream`, no
  * allocation. */
 dtst_status dtst_inverse_block(dtst_plan_t p, const void* yhat, const float* x, const float* w_bypass, float* y,

@@ -206,8 +206,8 @@ int prepare_block_zt(const StreamCfg& c, int64_t ci, int64_t co, int* grid);
 int launch_inv_zt_block(const StreamCfg& c, int grid_resident, const void* in, const float* x, const float* w,
                         float* y, int64_t batch, int64_t nxy, int64_t ci, int64_t co, const float* timg,
                         const float* zimg, void* stream);
-// The same for the shapes outside the chunked kernel's unconditional passes
-// (k_block_row.hip), with the images of the z-first inverse.
+// The same by tasks of a wave, for few input channels (k_block_row.hip; Derived::blk
+// = 2), with the images of the z-first inverse.
 bool block_row_supported(const ZRowCfg& c, int64_t ci, int64_t co);
 int prepare_block_row(const ZRowCfg& c, int64_t ci, int64_t co, int* grid);
 int launch_inv_row_block(const ZRowCfg& c, const StreamCfg& s, int grid_resident, const void* in, const float* x,

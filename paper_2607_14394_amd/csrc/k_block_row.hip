@@ -2,12 +2,11 @@
 //
 //   y[b,o,n] = GELU( sum_i w[o,i] x[b,i,n] + Re sum_{kz,kt} C_t C_z V[b,o,kz,kt] ),
 //
-// V the y-expanded spectrum (B, C_out, N_x, N_y, K_z, K_t), for the shapes that
-// do not fill the unconditional passes of the chunked kernel (block_zt.h).  That
-// kernel runs one workgroup of two waves per SIMD in lock step, a barrier per
-// chunk of 16 z rows, and forms the bypass on 16-channel matrix tiles: with few
-// channels, ragged z or short t most of its lanes idle and each step costs a
-// memory latency (5 channels of 2 x 12 x 159 rows of 204 x 16, with the x and y
+// V the y-expanded spectrum (B, C_out, N_x, N_y, K_z, K_t), for few input channels.
+// The chunked kernel (block_zt.h) runs one workgroup of two waves per SIMD in lock
+// step, a barrier per chunk of z rows, and forms the bypass on 16-channel matrix
+// tiles: with few channels most of its lanes idle and each step costs a memory
+// latency (5 channels of 2 x 12 x 159 rows of 204 x 16, with the x and y
 // expansions: 545 us, here 209 us).
 //
 // Here a workgroup of 8 waves takes a few (b, x, y) rows at a time.  First the
@@ -22,7 +21,8 @@
 // tasks need no barrier.  Bound: HBM and the latency of a task's reads for few
 // channels, the vector unit above (C_in C_out FMAs and 15 C_out GELU
 // instructions per point), so plans take it up to 8 input channels (12 with one
-// t group).
+// t group); above 8 output channels not for short rows, whose expansion a group
+// pays per output channel (the rule, with figures, is where Derived::blk is set).
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
