@@ -6,8 +6,9 @@
 //   wgrad    g_w[m-m0,i,o] (+)= sum_b conj(xhat[b,i,m]) g_y[b,o,m]
 //
 // Row groups of lanes below; the column forms further down take C_out up to 64
-// (mix) or 63 (mix_h, wgrad) except at 16, and mostly 32, columns, where the row
-// groups measured faster (row_groups, and `lines` in launch_wgrad), and where
+// (mix) or 63 (mix_h, wgrad) except at 16, and mostly 32, columns and other widths
+// and mode counts where the row groups measured faster (row_groups, row_groups_h,
+// few_blocks, launch_mix, and `lines` in launch_wgrad), and where
 // their LDS does not fit.
 //
 // With B <= 2 the arithmetic intensity is about 1-2 flop/byte, so all three
@@ -863,10 +864,17 @@ bool row_groups(int64_t ci, int64_t co, int64_t modes) {
 // column (an odd C_out): an element of w then costs two LDS accesses an entry,
 // which the row groups' register sums do not, unless most of their lanes idle
 // (65536 modes, B = 3: 13 -> 13 29.6 us and 42.9 by columns, 29 -> 29 121 and 170,
-// 21 -> 21 80 and 76).
+// 21 -> 21 80 and 76; 49152 modes, B = 3: 10 -> 29 35.7 and 52.5).
 bool row_groups_h(int64_t B, int64_t ci, int64_t co) {
-  return co % 2 != 0 && B > 1 && (B * ci >= 32 || co > 32) && (co <= 7 || 10 * co >= 7 * lanes_per_row(co));
+  return co % 2 != 0 && B > 1 && (B * ci >= 32 || co >= 25) && (co <= 7 || 10 * co >= 7 * lanes_per_row(co));
 }
+
+// Several batch entries and few modes: the column forms' blocks, of about twice
+// the modes, leave CUs idle (2048 modes, B = 2, row groups and columns: 20 -> 20 mix
+// 6.3 and 7.6 us, mix_h 8.0 and 9.1; 28 -> 28 mix_h 9.1 and 12.0; 7680 modes, B = 3:
+// 14 -> 14 mix 6.5 and 8.1; with blocks enough columns are the faster, 8192 modes, B
+// = 2, 20 -> 20 mix_h by row groups 1.3 times the columns' time).
+bool few_blocks(int64_t B, int64_t blocks, int64_t least) { return B > 1 && blocks < least; }
 
 // Rows of w in flight: as many as C_in, or the count that leaves the fewest
 // unused ones; but 8 where the registers of 16 or 20 cost more waves than their
@@ -898,13 +906,16 @@ pair_fn pick_mix_h_cols(int r) {
 int launch_mix(const void* xhat, const void* w, void* yhat, int64_t B, int64_t ci, int64_t co, int64_t M,
                int64_t m0, int64_t m1, void* stream) {
   if (B <= 0 || m1 <= m0) return hipSuccess;
-  if (co <= 64 && !row_groups(ci, co, m1 - m0)) {
+  // (27 to 31 columns fill the row groups as well, which have twice the blocks: 28
+  // -> 28, 7680 modes, B = 2: 11.4 us and 14.8 by columns; 32768, B = 1: 31.8 and
+  // 32.8; 49152, B = 1: 60.5 and 57.9)
+  if (co <= 64 && !row_groups(ci, co, m1 - m0) && !(co >= 27 && co < 32)) {
     const int cols = cols_of(co, w), r = rows_in_flight(ci, ci >= 13 && ci <= 20);
     const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, 0);
     const size_t lds = sizeof(float2) * size_t(B) * size_t(ci + co) * (a.mpb + 1);
     // (with up to four columns a block is up to 256 modes, whose input spectra then
     // fill the LDS: 65536 modes of 20 -> 3, B = 3: 26.9 us, by row groups 16.9)
-    if (lds <= (co <= 4 && ci >= 12 ? 24 : 64) * 1024)
+    if (lds <= (co <= 4 && ci >= 12 ? 24 : 64) * 1024 && !few_blocks(B, a.nblk, 256))
       return launch_pair(cols == 2 ? pick_mix_cols<2>(r) : pick_mix_cols<1>(r), lds, xhat, w, yhat, a, stream);
   }
   const MixArgs a = make_args(B, ci, co, M, m0, m1, 0);
@@ -922,7 +933,7 @@ int launch_mix_h(const void* gy, const void* w, void* gx, int64_t B, int64_t ci,
     const int cols = cols_of(co, w), r = rows_in_flight(ci, B > 1 && ci >= 13 && co % 2 == 0 && co >= 12);
     const PairArgs a = pair_args(B, ci, co, M, m0, m1, cols, 0);
     const size_t lds = sizeof(float2) * (size_t(B) * size_t(ci + co) * (a.mpb + 1) + size_t(4) * r * 65);
-    if (lds <= 80 * 1024)
+    if (lds <= 80 * 1024 && !few_blocks(B, a.nblk, 129))
       return launch_pair(cols == 2 ? pick_mix_h_cols<2>(r) : pick_mix_h_cols<1>(r), lds, gy, w, gx, a, stream);
   }
   const MixArgs a = make_args(B, ci, co, M, m0, m1, 0);

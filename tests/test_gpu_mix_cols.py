@@ -18,13 +18,25 @@ CASES = [(1, 1, 1), (2, 3, 2), (1, 5, 5), (1, 20, 20), (3, 4, 6), (2, 21, 9), (1
 
 @pytest.mark.parametrize("b,ci,co", CASES)
 def test_mix_and_gradients(b, ci, co):
+    parity((6, 8, 8, 8), (2, 3, 3), 3, b, ci, co, lambda M: ((0, M), (5, 5 + 137), (M - 1, M)))
+
+
+@pytest.mark.parametrize("b,ci,co", [c for c in CASES if c[0] > 1 and c[2] <= 64] + [(2, 10, 29), (3, 28, 28), (2, 6, 26)])
+def test_columns_of_several_batch_entries(b, ci, co):
+    """Column forms with B > 1, which take over from the row groups at 256 blocks of 4 x 64 / (C_out / W) modes: one
+    block fewer, and that many with a ragged last one."""
+    modes = 4 * (64 // (co // (2 if co % 2 == 0 else 1)))
+    parity((32, 32, 16, 8), (16, 16, 8), 5, b, ci, co,
+           lambda M: ((6, 6 + 255 * modes), (6, 6 + 255 * modes + 1), (7, 7 + 128 * modes + 1)))
+
+
+def parity(n, k, kt, b, ci, co, ranges):
     torch = torch_gpu()
     import paper_2607_14394_amd as D
-    n = (6, 8, 8, 8)
-    g = geometry(n, n, (0, 0, 0, 0), (2, 3, 3), 3, b, ci, co)
+    g = geometry(n, n, (0, 0, 0, 0), k, kt, b, ci, co)
     plan = D.Plan(desc_of(g))
     M = plan.n_modes
-    for m0, m1 in ((0, M), (5, 5 + 137), (M - 1, M)):
+    for m0, m1 in ranges(M):
         say(f"[mix columns] B={b} {ci}->{co} modes [{m0}, {m1})")
         x, gy = rand_cplx((b, ci) + g.K, 81), rand_cplx((b, co) + g.K, 82)
         w, g0 = rand_cplx((m1 - m0, ci, co), 83), rand_cplx((m1 - m0, ci, co), 84)
