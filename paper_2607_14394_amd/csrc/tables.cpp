@@ -488,9 +488,13 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     // So they are for rows short for more than 8 output channels, N_z N_t below 40
     // sqrt(C_in C_out) (16 x 65 rows of 16 x 32, 8 -> 30 channels: 76 -> 156; 18
     // such of 294 random blocks: 0.42 to 1.05 of the chunks' rate, but for one of
-    // 1.7; 8 or fewer: 26 x 8, 6 channels, 41 -> 28).
+    // 1.7; 8 or fewer: 26 x 8, 6 channels, 41 -> 28), or of up to 48 z where two t
+    // groups expand two k_t tiles (23 x 60 rows of 38 x 32, K_t 10, 5 -> 16, B = 2:
+    // 176 -> 215; 9 such blocks 0.72 to 0.93 of the chunks' rate but for one of two
+    // input channels, 1.19; longer rows 0.93 to 2.2).
     const int64_t row = int64_t(sc.nz) * sc.nt;
-    const bool filled = d->c_out <= 8 || row * row >= int64_t(1600) * d->c_in * d->c_out;
+    const bool filled = d->c_out <= 8 || (row * row >= int64_t(1600) * d->c_in * d->c_out &&
+                                          !(sc.th == 2 && sc.kt > 8 && sc.nz <= 48));
     if (dv.blk && (d->c_in <= 8 || (d->c_in <= 12 && sc.th == 1)) && filled &&
         block_row_supported(dv.zr, d->c_in, d->c_out))
       dv.blk = 2;

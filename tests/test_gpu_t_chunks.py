@@ -159,7 +159,7 @@ def test_inverse_block_z_runs(nt, nz, c):
 
 # (n, k_max z, k_t, C_in, C_out, shard): row tasks of few input channels
 ROW_BLOCKS = [((2, 3, 204, 16), 19, 4, 5, 5, None), ((3, 7, 27, 8), 13, 3, 4, 4, None),
-              ((2, 5, 36, 32), 13, 5, 7, 7, None), ((2, 3, 30, 30), 8, 16, 8, 32, None),
+              ((2, 5, 36, 32), 13, 5, 7, 7, None), ((2, 3, 50, 30), 8, 16, 8, 32, None),
               ((2, 3, 31, 8), 9, 3, 12, 3, None), ((2, 2, 40, 12), 16, 7, 1, 2, (9, 17)), ((5, 61, 2, 6), 1, 2, 3, 1, None),
               ((9, 40, 50, 32), 6, 9, 2, 5, None)]
 
@@ -167,7 +167,8 @@ ROW_BLOCKS = [((2, 3, 204, 16), 19, 4, 5, 5, None), ((3, 7, 27, 8), 13, 3, 4, 4,
 # few input channels, and rows too short for their output channels to be row tasks: chunks
 SHORT_ROWS = [((4, 13, 16, 32), 7, 7, 8, 30, None), ((3, 11, 20, 10), 8, 4, 9, 32, None),
               ((4, 7, 14, 20), 5, 7, 4, 20, None), ((2, 9, 16, 8), 5, 3, 1, 32, None),
-              ((2, 9, 25, 12), 4, 3, 6, 17, (11, 9))]
+              ((2, 9, 25, 12), 4, 3, 6, 17, (11, 9)), ((2, 3, 30, 30), 8, 16, 8, 32, None),
+              ((3, 5, 38, 32), 10, 10, 5, 16, None)]
 
 
 @pytest.mark.parametrize("case", ROW_BLOCKS + SHORT_ROWS, ids=lambda c: "x".join(map(str, c[0])) + f"_c{c[3]}_{c[4]}")
