@@ -36,7 +36,8 @@ struct StreamCfg {
   int zt = 0;   // ceil(zh / 16)
   int kcp = 0;  // padded slots per class = 8*mt
   int vec = 0;  // 1 when N_t >= 4 (16-byte row chunks, at any 4-byte alignment)
-  // 1 when t folds: CT = 2, TH = 2 and the shard holds the whole even t extent
+  // 1 when t folds: CT = 2, TH = 2 and the shard holds the whole t extent, 32, or,
+  // in Derived::sb, any even one
   // (the t images then hold the folded layout of the split kernels)
   int tf = 0;
   size_t lds_bytes = 0;

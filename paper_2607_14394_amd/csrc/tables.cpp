@@ -244,14 +244,19 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   sc.zt = static_cast<int>(ceil_div(sc.zh, 16));
   sc.vec = sc.nt >= 4 ? 1 : 0;
   // t folds (even k_t from x(t) + x(t + N_t/2), odd k_t from the difference)
-  // in the split kernels when the shard holds the whole even t extent and
-  // each half is one 16-wide group (17 <= N_t <= 32; the kernels read the two
-  // halves at any 4-byte alignment).  Its z image is half as large again as
-  // the unfolded one: where only the unfolded one fits the LDS, N_t != 32 stays
-  // unfolded (N_t = 32 always folds).
+  // in the split kernels when the shard holds the whole N_t = 32.  Shorter even
+  // N_t would fold too (each half is one 16-wide group from 18), 7% faster over 40
+  // random geometries, but the three-product z step that goes with it made the
+  // forward's error 10% larger (up to 20%: 32 x 16 x 154 x 28 2.4e-7 -> 2.9e-7) and the
+  // inverse's 2%: only the block kernel, below, folds those, where its z image, half
+  // as large again, fits the LDS.
   auto z_lds = [&] { return size_t(sc.ncls) * sc.zt * z_blocks(sc) * 64 * 16; };
   sc.tf = (sc.ct == 2 && sc.th == 2 && sc.nt % 2 == 0 && d->n_local[3] == d->n_global[3]) ? 1 : 0;
-  if (sc.nt != 32 && z_lds() > 160 * 1024) sc.tf = 0;
+  StreamCfg folded = sc;
+  if (sc.nt != 32) {
+    if (z_lds() > 160 * 1024) folded.tf = 0;
+    sc.tf = 0;
+  }
   sc.lds_bytes = z_lds();
   if (sc.lds_bytes > 160 * 1024) {
     *err = "z basis image exceeds the 160 KiB LDS of a workgroup";
@@ -348,6 +353,9 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   // conditions on y (also for K_t > 8, which the t-first fused kernel does not
   // cover), with the plane in `parts` where the workspace holds the parts.
   if (ZRowCfg z; z_first(sc, d->n_local[2] == d->n_global[2], &z)) {
+    // The forward goes z first only where that takes fewer than even t-folded rows
+    // would: between the two counts the rows t first, unfolded, were 5% faster (40
+    // geometries), and z first the inverse.
     const int tcost = t_first_cost(sc);
     z.ncy = fold_y ? 2 : 1;
     z.kyt = fold_y ? dv.ay_f.kth : dv.ay_f.ktiles;
@@ -355,7 +363,12 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     z.fused_mrow = static_cast<int>(round_up(mcols, 32)) + 16;
     z.fused_lds_bytes = size_t(dv.ay_f.ktiles) * dv.ay_f.JQ * 2 * 64 * 16 + size_t(16) * z.ncy * z.fused_mrow * 8 +
                         size_t(z.units) * z.ntl * 2 * 64 * 16;
-    const bool fwd_better = z_first_fwd_cost(z) < tcost;
+    // Against four z classes and K_t > 8 (so more than 32 modes: two mode tiles, two
+    // chains of which would not fit) the rows z first took 10 to 15% less time, but
+    // their error was 3 to 13% larger forward and 2 to 6% inverse: t first, except at
+    // N_t = 32, whose folded rows' error is as large.
+    const bool precise = !(sc.ct == 2 && sc.ncls == 4 && !sc.tf);
+    const bool fwd_better = precise && z_first_fwd_cost(z) < t_first_cost(folded);
     // Separate launches (where the plan has W1) stay where the fused kernel's two
     // waves per SIMD do not carry the row work: two mode tiles (28 x 24 x 86 x 32,
     // K_z 36: 86 us separate), or one t group (99 x 90 x 75 x 10: 289, fused 333);
@@ -394,7 +407,7 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     }
     z.ifused_lds_bytes = size_t(dv.ay_i.ktiles) * dv.ay_i.JQ * (fold_y ? 2 : 1) * 2 * 64 * 16 +
                          size_t(16) * z.ncy * z.fused_mrow * 8 + size_t(z.units) * z.ns * 64 * 8;
-    if (z_first_inv_cost(z) < tcost) {
+    if (precise && z_first_inv_cost(z) < tcost) {
       if ((flags & DTST_PLAN_SPLIT_SCHEDULE) == 0 && mcols <= 256 && z.fold && dv.ay_i.JQ == z.kyt &&
           z.kyt <= (fold_y ? 1 : 2) && z.ifused_lds_bytes <= 160 * 1024 && bc * d->n_local[0] < (1 << 24))
         z.inv = 2;
@@ -451,6 +464,7 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
   // DTST_PLAN_UNFUSED_BLOCK keeps the inverse and the epilogue separate.
   {
     StreamCfg sb = sc;
+    sb.tf = folded.tf;
     sb.ncls = fold && round_up(ceil_div(sc.kz, 2), 16) < round_up(sc.kz, 16) ? 2 : 1;
     sb.kcp = static_cast<int>(round_up(ceil_div(sc.kz, sb.ncls), 16));
     sb.mt = sb.kcp / 8;

@@ -92,12 +92,12 @@ def test_inverse_block(nt, kt, c):
 @pytest.mark.parametrize("n,kz,kt,c", [((2, 3, 288, 28), 8, 15, 20), ((2, 2, 388, 28), 5, 13, 20),
                                        ((2, 2, 386, 28), 10, 11, 16), ((2, 2, 480, 28), 8, 9, 32)])
 def test_inverse_block_long_z(n, kz, kt, c):
-    """t folds in the transforms and not in the fused block kernel, whose LDS the folded z image would exceed."""
+    """t does not fold in the fused block kernel where its LDS does not hold the folded z image."""
     torch = torch_gpu()
     import paper_2607_14394_amd as D
     g = geometry(n, n, (0, 0, 0, 0), (1, 1, kz), kt, 2, c, c)
     s = D.dtst_desc_schedule(desc_of(g))
-    assert s.t_folded and s.block == D.BLOCK_CHUNKS and not s.block_t_folded
+    assert s.block == D.BLOCK_CHUNKS and not s.block_t_folded
     say(f"[t chunks, long block] n={n} kt={kt} c={c}")
     plan = D.Plan(desc_of(g))
     yh, x = rand_cplx((2, c) + g.K, 51), rand_real((2, c) + n, 52)

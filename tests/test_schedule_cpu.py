@@ -29,7 +29,9 @@ def test_z_first_cases(name):
 @pytest.mark.parametrize("name", list(T_FIRST))
 def test_t_first_cases(name):
     s = schedule(T_FIRST[name])
-    assert s.forward == s.inverse == D.ROWS_T_FIRST and s.t_folded
+    n_t = T_FIRST[name][1][3]
+    assert s.forward == D.ROWS_T_FIRST and s.t_folded == (n_t == 32)
+    assert (s.inverse == D.ROWS_T_FIRST) == (n_t == 32)
 
 
 def test_z_first_cases_cover_the_unfolded_fused_forward():
@@ -96,7 +98,7 @@ LONG_BLOCKS = [((2, 3, 288, 28), 8, 15, 20, 20, True), ((2, 2, 388, 28), 5, 13, 
 def test_long_blocks_keep_the_fused_kernel_unfolded(case):
     n, kz, kt, ci, co, fused = case
     s = schedule((n, n, (0, 0, 0, 0), (1, 1, kz), kt, 2, ci, co))
-    assert s.t_folded
+    assert not s.t_folded
     assert (s.block, s.block_t_folded) == ((D.BLOCK_CHUNKS, 0) if fused else (D.BLOCK_SEPARATE, 1))
 
 
