@@ -482,7 +482,7 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     // (20 channels of 16 x 32 rows of 288 x 28, K_z 16: 340 us in two launches,
     // 235 fused; 8 x 32 rows of 388 x 28: 205, 183; of 386 x 28 in two classes, 16
     // channels: 153, 133), or one class and unconditional passes (32 channels of
-    // 480 x 28: 410, 327).  Two launches, with t folded, were faster elsewhere (28
+    // 480 x 28: 410, 327).  Two launches, measured with t folded, were faster elsewhere (28
     // channels of 402 x 28: 304, 316; 16 of 347 x 20, two tiles: 105, 149; 32 of
     // 384 x 20, two classes: 256, 306).  N_t = 32 is always folded.
     const int64_t cb = std::max(d->c_in, d->c_out);

@@ -137,7 +137,8 @@ def test_work_uses_stage_flops_and_folds():
 
 
 def test_work_follows_the_library_schedule():
-    """Products are counted for the kernels that a plan takes: t unfolded below N_t = 32, z first with mirrored rows, and z first on a shard of z."""
+    """Products are counted for the kernels that a plan takes: t unfolded below N_t = 32, z first with
+    mirrored rows, and z first on a shard of z."""
     import bench
     import paper_2607_14394_amd as D
 
