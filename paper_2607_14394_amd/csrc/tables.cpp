@@ -502,13 +502,13 @@ dtst_status derive(const dtst_desc* d, uint32_t flags, Derived* out, std::string
     // So they are for rows short for more than 8 output channels, N_z N_t below 40
     // sqrt(C_in C_out) (16 x 65 rows of 16 x 32, 8 -> 30 channels: 76 -> 156; 18
     // such of 294 random blocks: 0.42 to 1.05 of the chunks' rate, but for one of
-    // 1.7; 8 or fewer: 26 x 8, 6 channels, 41 -> 28), or of up to 48 z where two t
-    // groups expand two k_t tiles (23 x 60 rows of 38 x 32, K_t 10, 5 -> 16, B = 2:
-    // 176 -> 215; 9 such blocks 0.72 to 0.93 of the chunks' rate but for one of two
-    // input channels, 1.19; longer rows 0.93 to 2.2).
+    // 1.7; 8 or fewer: 26 x 8, 6 channels, 41 -> 28), or of two t groups and up to 40
+    // z, 48 with two k_t tiles to expand (23 x 60 rows of 38 x 32, K_t 5, 5 -> 16, B =
+    // 2: 175 -> 215; 8 x 72 of 47 x 32, K_t 9, 5 -> 12, B = 2: 0.81 of the chunks' rate;
+    // 24 such blocks 0.67 to 1.34, mean 0.89; longer rows 0.8 to 2.6, mean 1.4).
     const int64_t row = int64_t(sc.nz) * sc.nt;
     const bool filled = d->c_out <= 8 || (row * row >= int64_t(1600) * d->c_in * d->c_out &&
-                                          !(sc.th == 2 && sc.kt > 8 && sc.nz <= 48));
+                                          !(sc.th == 2 && sc.nz <= (sc.kt > 8 ? 48 : 40)));
     if (dv.blk && (d->c_in <= 8 || (d->c_in <= 12 && sc.th == 1)) && filled &&
         block_row_supported(dv.zr, d->c_in, d->c_out))
       dv.blk = 2;

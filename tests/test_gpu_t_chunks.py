@@ -168,7 +168,7 @@ ROW_BLOCKS = [((2, 3, 204, 16), 19, 4, 5, 5, None), ((3, 7, 27, 8), 13, 3, 4, 4,
 SHORT_ROWS = [((4, 13, 16, 32), 7, 7, 8, 30, None), ((3, 11, 20, 10), 8, 4, 9, 32, None),
               ((4, 7, 14, 20), 5, 7, 4, 20, None), ((2, 9, 16, 8), 5, 3, 1, 32, None),
               ((2, 9, 25, 12), 4, 3, 6, 17, (11, 9)), ((2, 3, 30, 30), 8, 16, 8, 32, None),
-              ((3, 5, 38, 32), 10, 10, 5, 16, None)]
+              ((3, 5, 38, 32), 10, 10, 5, 16, None), ((3, 5, 38, 32), 10, 5, 5, 16, None)]
 
 
 @pytest.mark.parametrize("case", ROW_BLOCKS + SHORT_ROWS, ids=lambda c: "x".join(map(str, c[0])) + f"_c{c[3]}_{c[4]}")
